@@ -102,24 +102,35 @@ struct CubicTileGeom {
 
 int cubic_tile_segs(int dim) { return 32 / (3 * dim) - 1; }
 
-__global__ __launch_bounds__(kBlock) void k_tile_cubic(const float *__restrict__ grid, int64_t n_seg, int dim,
-                                                       int segs, int64_t n_tiles, float *__restrict__ tiles) {
+// One thread per 16 bytes of a tile.
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_tile_cubic(const float *__restrict__ grid, int64_t n_seg, int64_t n_tiles,
+                                                       float *__restrict__ tiles) {
+    constexpr int W = CubicTileGeom<DIM>::W, S = CubicTileGeom<DIM>::S;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (i >= n_tiles * 32) return;
-    const int64_t j = i >> 5;
-    const int f = static_cast<int>(i & 31);
-    const int w = 3 * dim;
-    const int c = f / w, within = f - c * w;
-    const int part = within / dim, ch = within - part * dim;  // part 0: A, 1: x0, 2: x1
-    const int64_t col = j * segs + c;
-    float v = 0.0f;
-    if (c <= segs && col <= n_seg) {
+    if (i >= n_tiles * 8) return;
+    const int64_t j = i >> 3;
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int f = static_cast<int>(i & 7) * 4 + e;
+        const int c = f / W, within = f - c * W;
+        const int part = within / DIM, ch = within - part * DIM;  // part 0: A, 1: x0, 2: x1
+        const int64_t col = j * S + c;
         const int r = static_cast<int>(col & 1);
         const int layer = part == 2 ? 1 : 0;
         const int row = part == 0 ? r : 1 - r;
-        v = grid[((col * 2 + layer) * 2 + row) * dim + ch];
+        v[e] = c <= S && col <= n_seg ? grid[((col * 2 + layer) * 2 + row) * DIM + ch] : 0.0f;
     }
-    tiles[i] = v;
+    reinterpret_cast<float4 *>(tiles)[i] = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+template <int DIM>
+void launch_tile_cubic(const float *grid, int64_t n_seg, float *tiles, hipStream_t s) {
+    constexpr int S = CubicTileGeom<DIM>::S;
+    const int64_t n_tiles = (n_seg + S - 1) / S;
+    const uint32_t blocks = static_cast<uint32_t>((n_tiles * 8 + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(k_tile_cubic<DIM>, dim3(blocks), dim3(kBlock), 0, s, grid, n_seg, n_tiles, tiles);
 }
 
 template <int DIM, int QPT>
@@ -232,12 +243,13 @@ int bz_tile_piecewise_cubic(const float *grid, int64_t n_seg, int dim, float *ti
         if (n_seg < 1 || n_seg > (int64_t(1) << 31)) return fail(BZ_ERR_SHAPE, "%s: n_seg not in 1..2^31", fn);
         if (!grid || !tiles) return fail(BZ_ERR_NULL, "%s: grid and tiles are required", fn);
         if (!aligned(grid, 4) || !aligned(tiles, 16)) return fail(BZ_ERR_ALIGN, "%s: tiles need 16-byte alignment", fn);
-        const int segs = cubic_tile_segs(dim);
-        const int64_t n_tiles = (n_seg + segs - 1) / segs;
-        const int64_t total = n_tiles * 32;
-        const uint32_t blocks = static_cast<uint32_t>((total + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL(k_tile_cubic, dim3(blocks), dim3(kBlock), 0, as_stream(stream), grid, n_seg, dim, segs,
-                           n_tiles, tiles);
+        const hipStream_t s = as_stream(stream);
+        switch (dim) {
+            case 1: launch_tile_cubic<1>(grid, n_seg, tiles, s); break;
+            case 2: launch_tile_cubic<2>(grid, n_seg, tiles, s); break;
+            case 3: launch_tile_cubic<3>(grid, n_seg, tiles, s); break;
+            default: launch_tile_cubic<4>(grid, n_seg, tiles, s); break;
+        }
         BZ_CHECK_LAUNCH("k_tile_cubic");
         return BZ_OK;
     });
