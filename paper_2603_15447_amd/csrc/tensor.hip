@@ -1,11 +1,10 @@
 // Tensor-product Bezier surfaces and volumes (Sec. 2.2: the order splits
 // over the parameter axes) for gfx950.
 //
-//  k_tensor_grid   one patch per workgroup, nu x nv uniform grid.  When the
-//                  block size is a multiple of nv every thread keeps one grid
-//                  column b, contracts the control net with the v basis once
-//                  (isoline control points R_i(v_b)) and then needs only the
-//                  u basis and du+1 FMAs per coordinate for each of its points.
+//  k_tensor_grid   nu x nv uniform grids: a workgroup contracts the control net
+//                  with the v basis once per grid column (isoline control
+//                  points R_i(v_b), in LDS beside the u basis of its rows), then
+//                  du+1 FMAs per coordinate and point.
 //  k_tensor_points one object per wavefront, random (u,v[,w]) per query,
 //                  4 queries per lane, separable contraction w -> v -> u.
 //  k_tensor_mfma   bicubic 32x32 grids as a dense contraction on the matrix

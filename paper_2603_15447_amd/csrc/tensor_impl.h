@@ -3,13 +3,10 @@
 // (Sec. 2.2: the order splits over the parameter axes).  The contraction is
 // the same for both; only the per-axis basis differs.
 //
-//  k_tensor_grid   one patch per workgroup, nu x nv uniform grid.  When the
-//                  block size is a multiple of nv every thread keeps one grid
-//                  column b, contracts the net with the v basis once
-//                  (isoline coefficients R_i(v_b)) and then needs only the u
-//                  basis and du+1 FMAs per coordinate for each of its points;
-//                  the u basis of each row (nu <= block size) comes from a
-//                  table in LDS filled once per workgroup.
+//  k_tensor_grid   nu x nv uniform grids: a workgroup contracts the net with
+//                  the v basis once per grid column (isoline coefficients
+//                  R_i(v_b), shared through LDS with the u basis of its rows),
+//                  then du+1 FMAs per coordinate and point.
 //  k_tensor_points one object per wavefront, random (u,v[,w]) per query,
 //                  4 queries per lane, separable contraction w -> v -> u.
 #pragma once
@@ -52,141 +49,266 @@ __device__ __forceinline__ void basis_at(float x, float (&B)[D + 1]) {
 }
 
 // ------------------------------------------------------------------ VALU grid
-// Column-per-thread body of k_tensor_grid (nv divides the block size): each
-// thread keeps grid column b, contracts the net with the v basis once and
-// evaluates its points of that column with the u basis of their rows.  When nu <= block size the u
-// basis of every row is computed once per workgroup into the LDS table tab_u
-// (the divide and the basis cost more instructions than a row's FMAs and
-// stores).  NU, NV > 0 fix the grid size at compile time: the row loop
-// unrolls, with du = dv the column basis is a row of the same table, and each
-// column is contracted once, by one thread, and shared with the other threads
-// of that column through LDS; 0 takes nu, nv at run time.  Every variant evaluates the
-// same basis at the same parameters a/(nu-1), b/(nv-1).
-template <int DU, int DV, int DIM, typename T, int BASIS, int NU, int NV>
-__device__ __forceinline__ void grid_columns(const T *__restrict__ P, int nu_rt, int nv_rt, float du_den, float dv_den,
-                                             float *__restrict__ ob, int64_t plane, float *tab_u) {
-    constexpr int NCP = (DU + 1) * (DV + 1);
-    const int nu = NU > 0 ? NU : nu_rt;
-    const int nv = NV > 0 ? NV : nv_rt;
-    const int b = threadIdx.x % nv;
-    const int a0 = threadIdx.x / nv;
-    const int astep = kBlock / nv;
-    const bool table = nu <= kBlock;
-    if (table) {
-        if (static_cast<int>(threadIdx.x) < nu) {
-            float Bu[DU + 1];
-            basis_at<DU, BASIS>(static_cast<float>(threadIdx.x) / du_den, Bu);
+// Uniform nu x nv grids.  A workgroup takes `chunk` consecutive points of the
+// output: of the whole sequence of patches when a patch's rows and columns
+// both fit one workgroup's tables (the chunk may then cover several patches,
+// or parts of them), else of one strip of `cb` columns of one patch.  The u
+// basis of its rows and the isoline coefficients R[c][i] = sum_j Bv_j(b)
+// P[c][i][j] of its columns are formed once and shared through LDS; a point is
+// then one row of the u basis, one column of R and du+1 FMAs per coordinate.
+// The output's writes bound it: the LDS reads (16 bytes of the u basis and 16
+// per coordinate of R, each padded to whole 16-byte vectors) and about 35
+// vector instructions per 64 points both allow twice the write rate.
+struct GridArgs {
+    int nu, nv;
+    int cb, strips;         // columns of a strip, strips per patch
+    int chunk;              // points per workgroup
+    int rows, slots;        // table capacities: rows of the u basis, patches per chunk
+    uint32_t per_strip;     // workgroups per strip; 0: chunks of the whole sequence
+    uint32_t n;             // points of the sequence, or of one strip
+    uint32_t npts;          // points of a patch, or of one strip
+    FastDiv div_cb, div_npts;
+    int64_t plane, o0;
+    int same;               // whole sequence: the planes lie alike to the 64-byte lines
+};
+
+// Points of the sequence that a plane's store at p is past the last 128-byte line.
+__device__ __forceinline__ uint32_t line_offset(const float *p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p) >> 2) & 31u;
+}
+
+// Floats of one (coordinate, column) or row entry of the LDS tables.
+template <int DU>
+constexpr int kGridPad = (DU + 4) / 4 * 4;
+
+// The control net of patch k of the workgroup, widened.
+template <int N, typename T>
+__device__ __forceinline__ void load_net(const T *__restrict__ p, float (&v)[N]) {
+    if constexpr (std::is_same<T, float>::value) {
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-            for (int i = 0; i <= DU; ++i) tab_u[threadIdx.x * (DU + 1) + i] = Bu[i];
+        for (int e = 0; e + 4 <= N; e += 4) {
+            const f4u x = *reinterpret_cast<const f4u *>(p + e);
+            v[e] = x[0], v[e + 1] = x[1], v[e + 2] = x[2], v[e + 3] = x[3];
         }
-        __syncthreads();
-    }
-    // isoline coefficients of column b: R[c][i] = sum_j Bv_j(b) P[c][i][j]
-    auto contract = [&](float (&R)[DIM][DU + 1]) {
-        float Bv[DV + 1];
-        if constexpr (NU > 0 && NU == NV && DU == DV) {
 #pragma unroll
-            for (int j = 0; j <= DV; ++j) Bv[j] = tab_u[b * (DU + 1) + j];
-        } else {
-            basis_at<DV, BASIS>(static_cast<float>(b) / dv_den, Bv);
-        }
-#pragma unroll
-        for (int c = 0; c < DIM; ++c)
-#pragma unroll
-            for (int i = 0; i <= DU; ++i) {
-                float acc = Bv[0] * to_f32<T>(P[c * NCP + i * (DV + 1)]);
-#pragma unroll
-                for (int j = 1; j <= DV; ++j)
-                    acc = __builtin_fmaf(Bv[j], to_f32<T>(P[c * NCP + i * (DV + 1) + j]), acc);
-                R[c][i] = acc;
-            }
-    };
-    float R[DIM][DU + 1];
-    if constexpr (NU > 0) {
-        static_assert(NU <= kBlock && NU % (kBlock / NV) == 0, "fixed grids fill whole row steps");
-        // the first NV threads contract one column each; the kBlock / NV
-        // threads of a column share it through LDS
-        __shared__ __align__(16) float tab_r[NV * DIM * (DU + 1)];
-        if (static_cast<int>(threadIdx.x) < NV) {
-            float Rc[DIM][DU + 1];
-            contract(Rc);
-#pragma unroll
-            for (int c = 0; c < DIM; ++c)
-#pragma unroll
-                for (int i = 0; i <= DU; ++i) tab_r[(b * DIM + c) * (DU + 1) + i] = Rc[c][i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < DIM; ++c)
-#pragma unroll
-            for (int i = 0; i <= DU; ++i) R[c][i] = tab_r[(b * DIM + c) * (DU + 1) + i];
-        const uint32_t lo = static_cast<uint32_t>(a0 * NV + b);
-#pragma unroll
-        for (int k = 0; k < NU / (kBlock / NV); ++k) {
-            const int a = a0 + k * (kBlock / NV);
-            float Bu[DU + 1];
-#pragma unroll
-            for (int i = 0; i <= DU; ++i) Bu[i] = tab_u[a * (DU + 1) + i];
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) st_stream(ob + c * plane + (lo + k * kBlock), dot_basis<DU>(Bu, R[c]));
-        }
-        return;
-    }
-    contract(R);
-    float *__restrict__ oc = ob + a0 * nv + b;
-    if (table) {
-        for (int a = a0; a < nu; a += astep, oc += kBlock) {
-            float Bu[DU + 1];
-#pragma unroll
-            for (int i = 0; i <= DU; ++i) Bu[i] = tab_u[a * (DU + 1) + i];
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) st_stream(oc + c * plane, dot_basis<DU>(Bu, R[c]));
-        }
+        for (int e = N / 4 * 4; e < N; ++e) v[e] = p[e];
     } else {
-        for (int a = a0; a < nu; a += astep, oc += kBlock) {
-            float Bu[DU + 1];
-            basis_at<DU, BASIS>(static_cast<float>(a) / du_den, Bu);
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) st_stream(oc + c * plane, dot_basis<DU>(Bu, R[c]));
-        }
+        for (int e = 0; e < N; ++e) v[e] = to_f32<T>(p[e]);
     }
 }
 
 template <int DU, int DV, int DIM, typename T, int BASIS>
-__global__ __launch_bounds__(kBlock) void k_tensor_grid(const T *__restrict__ ctrl, int nu, int nv,
-                                                        float *__restrict__ out, int64_t plane, int64_t o0) {
-    constexpr int NCP = (DU + 1) * (DV + 1);
-    const uint32_t o = blockIdx.x;
-    const T *__restrict__ P = ctrl + static_cast<size_t>(o) * DIM * NCP;
-    const int npts = nu * nv;
-    float *__restrict__ ob = out + (o0 + o) * static_cast<int64_t>(npts);
-    const float du_den = nu > 1 ? static_cast<float>(nu - 1) : 1.0f;
-    const float dv_den = nv > 1 ? static_cast<float>(nv - 1) : 1.0f;
-    __shared__ __align__(16) float tab_u[kBlock * (DU + 1)];
-    if (kBlock % nv == 0) {
-        if (nu == 32 && nv == 32) grid_columns<DU, DV, DIM, T, BASIS, 32, 32>(P, nu, nv, du_den, dv_den, ob, plane, tab_u);
-        else grid_columns<DU, DV, DIM, T, BASIS, 0, 0>(P, nu, nv, du_den, dv_den, ob, plane, tab_u);
+__global__ __launch_bounds__(kBlock) void k_tensor_grid(const T *__restrict__ ctrl, GridArgs g, float *__restrict__ out) {
+    constexpr int NCP = (DU + 1) * (DV + 1), PAD = kGridPad<DU>;
+    extern __shared__ __align__(16) float lds[];
+    float *__restrict__ tab_u = lds;                   // [rows][PAD]
+    float *__restrict__ tab_r = lds + PAD * g.rows;    // [DIM][slots*cb][PAD]
+    // [q0, q0 + n): the chunk in the sequence (or strip); o: its first patch,
+    // s0: its first point there
+    const int64_t patch_pts = static_cast<int64_t>(g.nu) * g.nv;
+    float *__restrict__ seq = out + g.o0 * patch_pts;
+    uint32_t o, q0, s0, sh = 0;
+    int b0 = 0;
+    if (g.per_strip == 0) {
+        // every chunk but the first begins on a 128-byte line of plane 0, or of
+        // each plane (then up to 31 points earlier, which the tables cover)
+        sh = g.same ? line_offset(seq) : 31;
+        const uint32_t at = blockIdx.x * g.chunk;
+        q0 = at > sh ? at - sh : 0;
+        o = fdiv(q0, g.div_npts);
+        s0 = q0 - o * g.npts;
     } else {
-        for (int p = threadIdx.x; p < npts; p += kBlock) {
-            const int a = p / nv, b = p - (p / nv) * nv;
-            float Bu[DU + 1], Bv[DV + 1];
-            basis_at<DU, BASIS>(static_cast<float>(a) / du_den, Bu);
-            basis_at<DV, BASIS>(static_cast<float>(b) / dv_den, Bv);
+        const uint32_t r = blockIdx.x / g.per_strip;
+        o = r / g.strips;
+        b0 = static_cast<int>(r - o * g.strips) * g.cb;
+        s0 = q0 = (blockIdx.x - r * g.per_strip) * g.chunk;
+    }
+    const uint32_t end = min(g.n, g.per_strip == 0 ? (blockIdx.x + 1) * g.chunk - (g.same ? sh : 0) : q0 + g.chunk);
+    const int n = static_cast<int>(end - q0);
+    if (n <= 0) return;
+    const int n_slots = static_cast<int>(fdiv(s0 + n - 1, g.div_npts)) + 1;
+    const int cols = min(g.cb, g.nv - b0);
+    // rows of the chunk: those of its one patch that it touches, or all
+    const int a_lo = n_slots == 1 ? static_cast<int>(fdiv(s0, g.div_cb)) : 0;
+    const int a_hi = n_slots == 1 ? static_cast<int>(fdiv(s0 + n - 1, g.div_cb)) : g.nu - 1;
+    const float du_den = g.nu > 1 ? static_cast<float>(g.nu - 1) : 1.0f;
+    const float dv_den = g.nv > 1 ? static_cast<float>(g.nv - 1) : 1.0f;
+    const T *__restrict__ P = ctrl + static_cast<size_t>(o) * DIM * NCP;
+    const int n_cols = g.slots * g.cb;
+    // (one patch: its net is the same for all threads and comes in by scalar loads)
+    auto contract = [&](const T *__restrict__ net, int e, int b) {
+        float N[DIM * NCP], Bv[DV + 1];
+        load_net<DIM * NCP>(net, N);
+        basis_at<DV, BASIS>(static_cast<float>(b0 + b) / dv_den, Bv);
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) {
-                float Ri[DU + 1];
+        for (int c = 0; c < DIM; ++c)
 #pragma unroll
-                for (int i = 0; i <= DU; ++i) {
-                    float acc = Bv[0] * to_f32<T>(P[c * NCP + i * (DV + 1)]);
+            for (int i = 0; i <= DU; ++i) {
+                float acc = Bv[0] * N[c * NCP + i * (DV + 1)];
 #pragma unroll
-                    for (int j = 1; j <= DV; ++j)
-                        acc = __builtin_fmaf(Bv[j], to_f32<T>(P[c * NCP + i * (DV + 1) + j]), acc);
-                    Ri[i] = acc;
-                }
-                st_stream(ob + c * plane + p, dot_basis<DU>(Bu, Ri));
+                for (int j = 1; j <= DV; ++j) acc = __builtin_fmaf(Bv[j], N[c * NCP + i * (DV + 1) + j], acc);
+                tab_r[(c * n_cols + e) * PAD + i] = acc;
             }
+    };
+    if (n_slots == 1) {
+        if (static_cast<int>(threadIdx.x) < g.cb) contract(P, threadIdx.x, threadIdx.x);
+    } else {
+        for (int e = threadIdx.x; e < n_slots * g.cb; e += kBlock) {
+            const int k = static_cast<int>(fdiv(e, g.div_cb));
+            contract(P + static_cast<size_t>(k) * DIM * NCP, e, e - k * g.cb);
         }
     }
+    // the u basis from the block's other end: its last waves have no columns while there are few
+    for (int a = kBlock - 1 - threadIdx.x; a <= a_hi - a_lo; a += kBlock) {
+        float Bu[DU + 1];
+        basis_at<DU, BASIS>(static_cast<float>(a_lo + a) / du_den, Bu);
+#pragma unroll
+        for (int i = 0; i <= DU; ++i) tab_u[a * PAD + i] = Bu[i];
+    }
+    __syncthreads();
+    // coordinate c of the point in row a, column b of patch k of the chunk
+    auto point = [&](int c, const float (&Bu)[DU + 1], uint32_t k, uint32_t b) {
+        float R[DU + 1];
+#pragma unroll
+        for (int i = 0; i <= DU; ++i) R[i] = tab_r[(c * n_cols + k * g.cb + b) * PAD + i];
+        return dot_basis<DU>(Bu, R);
+    };
+    auto row = [&](uint32_t a, float (&Bu)[DU + 1]) {
+#pragma unroll
+        for (int i = 0; i <= DU; ++i) Bu[i] = tab_u[(a - a_lo) * PAD + i];
+    };
+    if (g.per_strip != 0) {
+        float *__restrict__ ob = seq + o * patch_pts + b0;
+        for (int p = threadIdx.x; p < n; p += kBlock) {
+            const uint32_t a = fdiv(s0 + p, g.div_cb), b = s0 + p - a * g.cb;
+            if (static_cast<int>(b) >= cols) continue;  // a patch's last strip is narrower
+            float Bu[DU + 1];
+            row(a, Bu);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) ob[c * g.plane + a * g.nv + b] = point(c, Bu, 0, b);
+        }
+        return;
+    }
+    // whole sequence: in plain order where the planes lie alike, else by way of
+    // LDS, from where each plane's own points, up to 31 apart, are stored so that
+    // every wave fills whole lines of it
+    float *__restrict__ buf = tab_r + PAD * DIM * n_cols;  // [DIM][chunk + 32]
+    const int pitch = g.chunk + 32;
+    // every point of the chunk; a full chunk's four per thread without bounds
+    // checks between them, so that their LDS reads overlap
+    auto each = [&](auto f) {
+        if (n == 4 * kBlock) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f(i);
+        } else {
+            for (int i = 0; static_cast<int>(threadIdx.x) + i * kBlock < n; ++i) f(i);
+        }
+    };
+    auto points = [&](auto same) {
+        auto put = [&](int c, int p, float v) {
+            if constexpr (decltype(same)::value) st_stream(seq + c * g.plane + q0 + p, v);
+            else buf[c * pitch + p] = v;
+        };
+        if (n_slots == 1 && kBlock % g.cb == 0) {
+            // one patch and whole rows per step: a thread stays in its column and
+            // keeps that column's coefficients (32 x 32 grids: 42 -> 35 us)
+            const uint32_t a = fdiv(s0 + threadIdx.x, g.div_cb), b = s0 + threadIdx.x - a * g.cb;
+            const uint32_t step = kBlock / g.cb;
+            float R[DIM][DU + 1];
+#pragma unroll
+            for (int c = 0; c < DIM; ++c)
+#pragma unroll
+                for (int i = 0; i <= DU; ++i) R[c][i] = tab_r[(c * n_cols + b) * PAD + i];
+            each([&](int i) {
+                float Bu[DU + 1];
+                row(a + i * step, Bu);
+#pragma unroll
+                for (int c = 0; c < DIM; ++c) put(c, threadIdx.x + i * kBlock, dot_basis<DU>(Bu, R[c]));
+            });
+            return;
+        }
+        each([&](int i) {
+            const int p = threadIdx.x + i * kBlock;
+            const uint32_t k = fdiv(s0 + p, g.div_npts), r = s0 + p - k * g.npts;
+            const uint32_t a = fdiv(r, g.div_cb), b = r - a * g.cb;
+            float Bu[DU + 1];
+            row(a, Bu);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) put(c, p, point(c, Bu, k, b));
+        });
+    };
+    if (g.same) {
+        points(std::true_type{});
+        return;
+    }
+    points(std::false_type{});
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+        float *__restrict__ oc = seq + c * g.plane;
+        const uint32_t first = blockIdx.x * g.chunk - line_offset(oc);  // may lie before 0: wraps
+        for (uint32_t p = threadIdx.x; p < static_cast<uint32_t>(g.chunk); p += kBlock) {
+            const uint32_t q = first + p;
+            if (q < g.n) st_stream(oc + q, buf[c * pitch + (q - q0)]);
+        }
+    }
+}
+
+// Layout of a grid call.  1024 points per workgroup (four per thread): short
+// workgroups write faster than long ones (32 x 32 grids of 16384 bicubic 3D
+// patches: 34.7 us with 1024, 37 with 2048, 42 with 4096, 47 with 512), fewer
+// points where a call is too small to give every CU four workgroups or the
+// tables of so many points would leave a CU too few workgroups.
+// Results go past the caches, for which each wave's store has to fill whole
+// lines: chunks begin on a line, and where the planes don't lie alike (their
+// distance is no multiple of 64 bytes), each plane's part of the chunk does.
+// 16384 patches of 33 x 33 points: 75 us with a patch per workgroup from its
+// first point on, 35 now; one patch more, whose planes don't lie alike: 48, and
+// 53 with ordinary stores in the order of evaluation.
+constexpr size_t kGridTableFloats = 10240;
+
+template <int DU, int DIM>
+size_t grid_floats(const GridArgs &g) {
+    return kGridPad<DU> * (g.rows + static_cast<size_t>(DIM) * g.slots * g.cb) +
+           (g.per_strip == 0 && !g.same ? static_cast<size_t>(DIM) * (g.chunk + 32) : 0);
+}
+
+template <int DU, int DIM>
+GridArgs grid_args(int nu, int nv, int64_t n_obj, int64_t plane) {
+    GridArgs g{};
+    g.nu = nu;
+    g.nv = nv;
+    g.plane = plane;
+    g.same = plane % 16 == 0 || DIM == 1;
+    const int64_t npts = static_cast<int64_t>(nu) * nv, total = n_obj * npts;
+    const int want = total >= int64_t(1024) * 256 ? 1024 : total >= int64_t(512) * 256 ? 512 : 256;
+    bool seq = false;
+    if (nu <= kBlock && nv <= kBlock) {
+        g.strips = 1;
+        g.cb = nv;
+        g.npts = static_cast<uint32_t>(npts);
+        g.rows = nu;
+        for (int chunk = want; chunk >= 256 && !seq; chunk /= 2) {
+            g.chunk = g.same ? chunk : chunk - 32;  // with the planes' own first points a whole number per thread
+            g.slots = static_cast<int>((g.chunk + 31 + npts - 2) / npts + 1);
+            seq = grid_floats<DU, DIM>(g) <= kGridTableFloats;
+        }
+    }
+    if (!seq) {  // long rows or columns, or rows too few to share a column's contraction
+        g.strips = (nv + kBlock - 1) / kBlock;
+        g.cb = (nv + g.strips - 1) / g.strips;
+        g.strips = (nv + g.cb - 1) / g.cb;
+        g.chunk = std::max(want, 8 * g.cb);  // a strip's columns are contracted once per chunk
+        g.npts = g.n = static_cast<uint32_t>(nu) * g.cb;
+        g.per_strip = (g.n + g.chunk - 1) / g.chunk;
+        g.slots = 1;
+        g.rows = std::min(nu, g.chunk / g.cb + 2);
+    }
+    g.div_cb = make_fastdiv(g.cb);
+    g.div_npts = make_fastdiv(g.npts);
+    return g;
 }
 
 // ------------------------------------------------------------------ VALU points
@@ -257,10 +379,22 @@ __global__ __launch_bounds__(kBlock) void k_tensor_points(const T *__restrict__ 
 
 // ------------------------------------------------------------------ dispatch (over degrees and dim)
 template <typename T, int BASIS, int DU, int DV, int DIM>
-void launch_grid3(const void *ctrl, int nu, int nv, float *out, int64_t plane, int64_t o0, uint32_t blocks,
+void launch_grid3(const void *ctrl, int nu, int nv, float *out, int64_t plane, int64_t o0, uint32_t n_obj,
                   hipStream_t s) {
-    hipLaunchKernelGGL((k_tensor_grid<DU, DV, DIM, T, BASIS>), dim3(blocks), dim3(kBlock), 0, s,
-                       static_cast<const T *>(ctrl), nu, nv, out, plane, o0);
+    GridArgs g = grid_args<DU, DIM>(nu, nv, n_obj, plane);
+    const size_t lds = sizeof(float) * grid_floats<DU, DIM>(g);
+    const int64_t npts = static_cast<int64_t>(nu) * nv;
+    // at most 2^30 points and 2^23 workgroups per launch (a patch has at most 2^24 points)
+    const int64_t per = g.per_strip == 0 ? (int64_t(1) << 30) / npts
+                                         : std::max<int64_t>(1, (int64_t(1) << 23) / (static_cast<int64_t>(g.per_strip) * g.strips));
+    for (int64_t p0 = 0; p0 < n_obj; p0 += per) {
+        const int64_t np = std::min<int64_t>(per, n_obj - p0);
+        if (g.per_strip == 0) g.n = static_cast<uint32_t>(np * npts);
+        g.o0 = o0 + p0;
+        const int64_t blocks = g.per_strip == 0 ? (np * npts + 31 + g.chunk - 1) / g.chunk : np * g.per_strip * g.strips;
+        hipLaunchKernelGGL((k_tensor_grid<DU, DV, DIM, T, BASIS>), dim3(static_cast<uint32_t>(blocks)), dim3(kBlock),
+                           lds, s, static_cast<const T *>(ctrl) + p0 * DIM * (DU + 1) * (DV + 1), g, out);
+    }
 }
 
 template <typename T, int BASIS, int DU, int DV>
