@@ -125,24 +125,19 @@ int bz_eval_rational(const void *ctrl, const void *w, int dtype, int64_t n_curve
  *        (x_k + x_{k+1})/2 = M_k (the diagonal texels of segment k average
  *        to its middle control point).  The free texels are formed by an
  *        FP64 alternating prefix sum and rounded once to FP32.
- * Uses a small stream-ordered device workspace (hipMallocAsync).
+ * Allocates nothing: block sums pass through grid itself, which must not
+ * overlap chain.
  */
 int bz_encode_piecewise(const float *chain, int64_t n_seg, int dim, float *grid, bz_stream stream);
 
 /*
- * Allocation-free variant of bz_encode_piecewise, for callers that cannot
- * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc).  Same arguments, same results bit for
- * bit; it allocates nothing (no hipMalloc, hipMallocAsync or hipFree): the
- * encoder's block partials live in a fixed 2 MiB device array of the library
- * (a copy per device, held until the process ends), whose address is looked
- * up once per device on the first call with that device current.  Limit: the
- * partials of ceil((n_seg+1)/2048) blocks x dim coordinates must fit 2^18
- * doubles, i.e. n_seg <= floor(2^18/dim)*2048 - 1 (536870911, 268435455,
- * 178956287, 134217727 for dim 1..4); larger n_seg returns BZ_ERR_SHAPE.
- * Every call on one device uses that device's one array: calls that overlap
- * in time on one device (different streams or threads) race and must be
- * serialised by the caller.  The array needs no clearing between calls.
+ * Variant of bz_encode_piecewise with a stated size limit, for callers that
+ * must not allocate device memory (code under HIP graph capture, tight serving
+ * loops, harnesses that forbid hipMalloc).  Same arguments, same results bit
+ * for bit; it allocates nothing and keeps no state, so calls may overlap on
+ * different streams or threads.  Limit: n_seg <= floor(2^18/dim)*2048 - 1
+ * (536870911, 268435455, 178956287, 134217727 for dim 1..4); larger n_seg
+ * returns BZ_ERR_SHAPE.
  */
 int bz_encode_piecewise_noalloc(const float *chain, int64_t n_seg, int dim, float *grid, bz_stream stream);
 

@@ -219,9 +219,8 @@ def encode_piecewise(chain, out=None):
 
 
 def encode_piecewise_noalloc(chain, out):
-    """As encode_piecewise, through the allocation-free entry point (its
-    workspace is the library's fixed per-device array); out is required, so
-    nothing is allocated on this path either."""
+    """As encode_piecewise, through the allocation-free entry point; out is
+    required, so nothing is allocated on this path either."""
     m, dim = chain.shape
     nseg = (m - 1) // 2
     assert m == 2 * nseg + 1

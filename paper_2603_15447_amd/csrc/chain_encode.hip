@@ -1,12 +1,10 @@
 // Zig-zag encoder of C0 piecewise chains (Sec. 2.1, Eq. 2, Fig. 2): the free
 // texels of a chain of N segments are fixed by x_0 = M_0 and x_k + x_{k+1} =
 // 2 M_k, an alternating prefix sum over the middle points, evaluated here as
-// an FP64 block scan (per-block partials, then one pass that adds up the
-// partials before its block, scans its own columns and writes them): every
-// texel is one FP32 rounding of an FP64 prefix sum, where an FP32 recurrence
-// x_{k+1} = 2 M_k - x_k would let the rounding error grow with k.
-#include <mutex>
-
+// an FP64 block scan (per-block sums, a scan of those, then one pass that
+// scans each block's own columns and writes them): every texel is one FP32
+// rounding of an FP64 prefix sum, where an FP32 recurrence x_{k+1} = 2 M_k -
+// x_k would let the rounding error grow with k.
 #include "common.h"
 
 namespace bzi {
@@ -29,23 +27,28 @@ namespace {
 // free texels in place of the middle points, and the block writes its part of
 // the grid in order.  A thread's columns take an odd number of LDS words, so
 // that the 64 lanes of a wave, all at the same place of their own run, meet
-// different banks.  (Threads reading their columns from global memory and
-// writing them there, a column pitch of 2*DIM floats apart, took 85 us for the
-// last pass alone at 2^20 3D segments, whose 50 MB a copy moves in 10.)
+// different banks.  At 2^20 3D segments the passes take 7 us (25 MB in), 5
+// and 12 us (25 MB in, 25 out).  (Threads that read and wrote their columns in
+// global memory, a column pitch of 2*DIM floats apart, took 18, 8 and 85 us;
+// with an LDS index computed per float instead of per four, the last pass was
+// bound by its index arithmetic and took 18.)
 constexpr int kEncPerThread = 4;
 
 template <int DIM, int ROWS, int NT>
 struct EncGeom {
     static constexpr int NCH = DIM * (ROWS - 1);
     static constexpr int COLS = NT * kEncPerThread;         // columns per block
-    static constexpr int RUN = kEncPerThread * ROWS * DIM;  // floats of a thread's columns
-    static constexpr int PITCH = RUN | 1;
+    static constexpr int RUN = kEncPerThread * ROWS * DIM;  // floats of a thread's columns in the chain,
+    static constexpr int OUT = kEncPerThread * 2 * NCH;     // and in the grid
     static constexpr int N = COLS * ROWS * DIM + (ROWS == 3 ? DIM : 0);  // floats staged
-    static constexpr int LDS = NT * PITCH + (ROWS == 3 ? DIM : 0);
+    static constexpr int LDS = NT * ((RUN > OUT ? RUN : OUT) | 1) + (ROWS == 3 ? DIM : 0);
     static constexpr int WAVES = NT / 64;
-    // LDS word of float f of the block's rows
-    static __device__ __forceinline__ int at(int f) { return f + (PITCH - RUN) * (f / RUN); }
 };
+
+// LDS word of float f, threads' runs of R floats (a multiple of 4, so four
+// floats from a multiple of 4 on lie together) an odd number of words apart.
+template <int R>
+__device__ __forceinline__ int enc_at(int f) { return f + f / R; }
 
 typedef float enc_f4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -56,19 +59,27 @@ __device__ __forceinline__ void enc_stage(const float *__restrict__ chain, int64
     const int64_t first = col0 * ROWS * DIM, total = (n_seg * ROWS + 1) * DIM;
     const float *__restrict__ src = chain + first;
     const int avail = static_cast<int>(min(static_cast<int64_t>(G::N), total - first));
-    for (int f = 4 * threadIdx.x; f < G::N; f += 4 * NT) {
-        float v[4] = {};
+    // all loads first: their latency passes once
+    constexpr int IT = (G::N + 4 * NT - 1) / (4 * NT);
+    float v[IT][4] = {};
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const int f = 4 * (threadIdx.x + i * NT);
         if (f + 4 <= avail) {
             const enc_f4 x = *reinterpret_cast<const enc_f4 *>(src + f);
-            v[0] = x[0], v[1] = x[1], v[2] = x[2], v[3] = x[3];
+            v[i][0] = x[0], v[i][1] = x[1], v[i][2] = x[2], v[i][3] = x[3];
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (f + e < avail) v[e] = src[f + e];
+                if (f + e < avail) v[i][e] = src[f + e];
         }
+    }
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const int f = 4 * (threadIdx.x + i * NT), at = enc_at<G::RUN>(f);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (G::N % 4 == 0 || f + e < G::N) lds[G::at(f + e)] = v[e];
+            if (f + e < G::N) lds[at + e] = v[i][e];
     }
 }
 
@@ -89,8 +100,9 @@ __device__ __forceinline__ void enc_elems(const float *lds, int64_t n_seg, int64
     const int64_t k0 = col0 + threadIdx.x * kEncPerThread;
 #pragma unroll
     for (int i = 0; i < kEncPerThread; ++i) {
-        const int f0 = (threadIdx.x * kEncPerThread + i) * ROWS * DIM;
-        auto row = [&](int j) { return lds[G::at(f0 + j)]; };
+        // (a last column's successor is the next thread's first)
+        const float *own = lds + threadIdx.x * (G::RUN | 1) + i * ROWS * DIM;
+        auto row = [&](int j) { return own[j + (i * ROWS * DIM + j >= G::RUN ? 1 : 0)]; };
 #pragma unroll
         for (int ch = 0; ch < G::NCH; ++ch) {
             const double m2 = enc_twice_mid<DIM, ROWS>(row, ch);
@@ -106,9 +118,23 @@ __device__ __forceinline__ double wave_sum64(double v) {
     return v;
 }
 
+// A block's sum (later: the sum before the block) waits in the first column of
+// the block's own part of the grid, NCH doubles in exactly one column: only
+// that block reads it in the last pass, before it writes the column, so the
+// encoder needs no workspace.  (hipMallocAsync and hipFreeAsync of a small one
+// cost 20 us of host time per call, more than all passes at 2^18 segments.)
+__device__ __forceinline__ void enc_put(float *p, int ch, double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    p[2 * ch] = __uint_as_float(static_cast<uint32_t>(u));
+    p[2 * ch + 1] = __uint_as_float(static_cast<uint32_t>(u >> 32));
+}
+__device__ __forceinline__ double enc_get(const float *p, int ch) {
+    return __builtin_bit_cast(double, __float_as_uint(p[2 * ch]) | static_cast<uint64_t>(__float_as_uint(p[2 * ch + 1])) << 32);
+}
+
 template <int DIM, int ROWS, int NT>
 __global__ __launch_bounds__(NT) void k_enc_partials(const float *__restrict__ chain, int64_t n_seg,
-                                                     double *__restrict__ partial) {
+                                                     float *__restrict__ grid) {
     using G = EncGeom<DIM, ROWS, NT>;
     __shared__ float lds[G::LDS];
     __shared__ double wsum[G::WAVES][G::NCH];
@@ -128,50 +154,58 @@ __global__ __launch_bounds__(NT) void k_enc_partials(const float *__restrict__ c
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < G::WAVES; ++w) s += wsum[w][threadIdx.x];
-        partial[static_cast<int64_t>(blockIdx.x) * G::NCH + threadIdx.x] = s;
+        enc_put(grid + col0 * 2 * G::NCH, threadIdx.x, s);
     }
 }
 
-// Exclusive scan of the block partials in place (one block, serial over
-// chunks), for chains of so many blocks that each block adding up its
-// predecessors' partials would read more than the chain itself.
-__global__ __launch_bounds__(kBlock) void k_enc_offsets(int nch, int64_t nb, double *__restrict__ partial) {
-    __shared__ double wsum[kBlock / 64];
+// Exclusive scan of the block sums in place: one workgroup, kScanThreads
+// blocks of the chain (`cols` columns each) at a time.
+constexpr int kScanThreads = 1024;
+
+template <int NCH>
+__global__ __launch_bounds__(kScanThreads) void k_enc_offsets(int64_t nb, int cols, float *__restrict__ grid) {
+    constexpr int WAVES = kScanThreads / 64;
+    __shared__ double wsum[WAVES][NCH];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int ch = 0; ch < nch; ++ch) {
-        double carry = 0.0;
-        for (int64_t b0 = 0; b0 < nb; b0 += kBlock) {
-            const int64_t b = b0 + threadIdx.x;
-            const double v = b < nb ? partial[b * nch + ch] : 0.0;
-            double incl = v;
+    double carry[NCH] = {};
+    for (int64_t b0 = 0; b0 < nb; b0 += kScanThreads) {
+        const int64_t b = b0 + threadIdx.x;
+        float *__restrict__ p = grid + b * cols * 2 * NCH;
+        double v[NCH], incl[NCH];
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) incl[ch] = v[ch] = b < nb ? enc_get(p, ch) : 0.0;
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
 #pragma unroll
             for (int off = 1; off < 64; off <<= 1) {
-                const double u = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += u;
+                const double u = __shfl_up(incl[ch], off, 64);
+                if (lane >= off) incl[ch] += u;
             }
-            if (lane == 63) wsum[wave] = incl;
-            __syncthreads();
-            double pre = carry;
-            for (int w = 0; w < wave; ++w) pre += wsum[w];
-            if (b < nb) partial[b * nch + ch] = pre + (incl - v);
-            for (int w = 0; w < kBlock / 64; ++w) carry += wsum[w];
-            __syncthreads();
+            if (lane == 63) wsum[wave][ch] = incl[ch];
         }
+        __syncthreads();
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+            double pre = carry[ch];
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {  // (unrolled: the LDS reads overlap)
+                const double t = wsum[w][ch];
+                carry[ch] += t;
+                pre += w < wave ? t : 0.0;
+            }
+            if (b < nb) enc_put(p, ch, pre + (incl[ch] - v[ch]));
+        }
+        __syncthreads();
     }
 }
-
-// Where a block finds the sum of the elements before its columns.
-enum {
-    kEncDirect = 0,   // adds up the chain before it (no workspace: chains of a few blocks)
-    kEncSelfSum = 1,  // adds up the partials before it
-    kEncScanned = 2   // k_enc_offsets has scanned the partials
-};
 
 // Writes the columns of a block: the endpoint in row k mod 2, the free texel
 // in the other row.  Output [N+1][layers][2][DIM] (layers = ROWS - 1).
-template <int DIM, int ROWS, int NT, int MODE>
+// DIRECT: the block adds up the chain before it itself (chains of a few
+// blocks, in one launch); otherwise the grid holds the sum before the block.
+template <int DIM, int ROWS, int NT, bool DIRECT>
 __global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chain, int64_t n_seg,
-                                                  const double *__restrict__ partial, float *__restrict__ grid) {
+                                                  float *__restrict__ grid) {
     using G = EncGeom<DIM, ROWS, NT>;
     constexpr int NCH = G::NCH;
     __shared__ float lds[G::LDS];
@@ -180,13 +214,10 @@ __global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chai
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     enc_stage<DIM, ROWS, NT>(chain, n_seg, col0, lds);
     double pre[NCH] = {};
-    if constexpr (MODE == kEncSelfSum) {
-        const int nb = static_cast<int>(blockIdx.x);
-#pragma unroll 2
-        for (int b = threadIdx.x; b < nb; b += NT)
+    if constexpr (!DIRECT) {
 #pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) pre[ch] += partial[static_cast<int64_t>(b) * NCH + ch];
-    } else if constexpr (MODE == kEncDirect) {
+        for (int ch = 0; ch < NCH; ++ch) pre[ch] = enc_get(grid + col0 * 2 * NCH, ch);
+    } else {
         const int n = static_cast<int>(col0);  // a multiple of NT: column parity is the thread's
 #pragma unroll 4
         for (int k = threadIdx.x; k < n; k += NT) {
@@ -201,6 +232,11 @@ __global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chai
     __syncthreads();
     double ev[kEncPerThread][NCH], incl[NCH], own[NCH];
     enc_elems<DIM, ROWS, NT>(lds, n_seg, col0, ev);
+    float A[kEncPerThread][DIM];
+#pragma unroll
+    for (int i = 0; i < kEncPerThread; ++i)
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) A[i][c] = lds[threadIdx.x * (G::RUN | 1) + i * ROWS * DIM + c];
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
         own[ch] = ((ev[0][ch] + ev[1][ch]) + ev[2][ch]) + ev[3][ch];
@@ -212,19 +248,20 @@ __global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chai
         }
         incl[ch] = v;
         if (lane == 63) wsum[wave][ch] = v;
-        if constexpr (MODE != kEncScanned) {
+        if constexpr (DIRECT) {
             const double p = wave_sum64(pre[ch]);
             if (lane == 0) wpre[wave][ch] = p;
         }
     }
-    __syncthreads();  // every thread has read its elements: their places may be overwritten
+    __syncthreads();  // every thread has read its columns: their places may be overwritten
+    float *run = lds + threadIdx.x * (G::OUT | 1);
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
         const float *__restrict__ c0 = chain;
         auto row = [&](int j) { return c0[j]; };
         double y = 0.5 * enc_twice_mid<DIM, ROWS>(row, ch);  // M_0
-        if constexpr (MODE == kEncScanned) {
-            y += partial[static_cast<int64_t>(blockIdx.x) * NCH + ch];
+        if constexpr (!DIRECT) {
+            y += pre[ch];
         } else {
 #pragma unroll
             for (int w = 0; w < G::WAVES; ++w) y += wpre[w][ch];
@@ -233,128 +270,79 @@ __global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chai
         for (int w = 0; w < G::WAVES; ++w)
             if (w < wave) y += wsum[w][ch];
         y += incl[ch] - own[ch];
+        const int layer = ch / DIM, c = ch - layer * DIM;
 #pragma unroll
         for (int i = 0; i < kEncPerThread; ++i) {
-            const int f0 = (threadIdx.x * kEncPerThread + i) * ROWS * DIM;
-            lds[G::at(f0 + DIM + ch)] = static_cast<float>((i & 1) ? -y : y);  // rows 1.. of the column: channel order
+            float *col = run + (i * (ROWS - 1) + layer) * 2 * DIM;
+            col[(i & 1) * DIM + c] = A[i][c];
+            col[(1 - (i & 1)) * DIM + c] = static_cast<float>((i & 1) ? -y : y);
             y += ev[i][ch];
         }
     }
     __syncthreads();
-    // grid float f of the block: column, layer, row, coordinate
     constexpr int GW = 2 * NCH;  // floats per grid column
-    const int64_t cols = min(static_cast<int64_t>(G::COLS), n_seg + 1 - col0);
-    const int nf = static_cast<int>(cols) * GW;
+    const int nf = static_cast<int>(min(static_cast<int64_t>(G::COLS), n_seg + 1 - col0)) * GW;
     float *__restrict__ dst = grid + col0 * GW;
-    auto texel = [&](int f) {
-        const int k = f / GW, r = f - k * GW;
-        const int layer = r / (2 * DIM), q = r - layer * 2 * DIM;
-        const int rw = q >= DIM, c = q - rw * DIM;
-        return lds[G::at(k * ROWS * DIM + (rw == (k & 1) ? c : DIM + layer * DIM + c))];
-    };
-    for (int f = 4 * threadIdx.x; f < nf; f += 4 * NT) {
-        enc_f4 v;
-        if (GW % 4 == 0 || f + 4 <= nf) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = texel(f + e);
+    for (int i = 0; i < G::OUT / 4; ++i) {
+        const int f = 4 * (threadIdx.x + i * NT), at = enc_at<G::OUT>(f);
+        if (f + 4 <= nf) {
+            enc_f4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = lds[at + e];
             *reinterpret_cast<enc_f4 *>(dst + f) = v;
         } else {
-            for (int e = 0; f + e < nf; ++e) dst[f + e] = texel(f + e);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (f + e < nf) dst[f + e] = lds[at + e];
         }
     }
 }
 
-// Partials of chains of up to kEncSmallCols columns come from blocks of 512
-// columns (128 threads), so that a chain of a few thousand segments still
-// spreads over the chip; longer chains take blocks of 2048 (512 threads), and
-// from kEncSelfSumMax blocks on one more launch scans the partials.  Chains of
-// up to kEncDirectCols columns go in one launch without a workspace.
-constexpr int kEncLongThreads = 512, kEncShortThreads = 128;
-constexpr int kEncPerBlock = kEncLongThreads * kEncPerThread;  // columns of a long chain's block
-constexpr int64_t kEncSmallCols = int64_t(1) << 18, kEncDirectCols = 4 * kEncPerBlock, kEncSelfSumMax = 4096;
+// Chains of up to kEncDirectCols columns go in one launch.  Chains of up to
+// kEncSmallCols columns take blocks of 512 columns (128 threads), so that a
+// chain of some ten thousand segments still spreads over the chip, longer ones
+// blocks of 2048 (512 threads), whose sums are fewer to scan.
+// (A cubic's columns are twice as wide: blocks of 1024.)
+constexpr int kEncShortThreads = 128;
+template <int ROWS>
+constexpr int kEncLongThreads = ROWS == 2 ? 512 : 256;
+constexpr int64_t kEncSmallCols = int64_t(1) << 18, kEncDirectCols = int64_t(1) << 15;
 
-struct EncPlan {
-    int64_t cols;  // columns per block
-    int64_t nb;    // blocks
-    int mode;
-};
-
-EncPlan enc_plan(int64_t n_seg) {
-    const int64_t n = n_seg + 1;
-    const bool direct = n <= kEncDirectCols;
-    const int64_t cols = !direct && n <= kEncSmallCols ? kEncShortThreads * kEncPerThread : kEncPerBlock;
-    const int64_t nb = (n + cols - 1) / cols;
-    return {cols, nb, direct ? kEncDirect : nb <= kEncSelfSumMax ? kEncSelfSum : kEncScanned};
+template <int DIM, int ROWS, int NT>
+void launch_encode_blocks(const float *chain, int64_t n_seg, float *grid, hipStream_t s) {
+    constexpr int COLS = EncGeom<DIM, ROWS, NT>::COLS, NCH = EncGeom<DIM, ROWS, NT>::NCH;
+    const int64_t nb = (n_seg + COLS) / COLS;
+    const dim3 blocks(static_cast<uint32_t>(nb));
+    hipLaunchKernelGGL((k_enc_partials<DIM, ROWS, NT>), blocks, dim3(NT), 0, s, chain, n_seg, grid);
+    hipLaunchKernelGGL((k_enc_offsets<NCH>), dim3(1), dim3(kScanThreads), 0, s, nb, COLS, grid);
+    hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NT, false>), blocks, dim3(NT), 0, s, chain, n_seg, grid);
 }
 
 template <int DIM, int ROWS>
-void launch_encode(const EncPlan &p, const float *chain, int64_t n_seg, double *partial, float *grid, hipStream_t s) {
-    constexpr int NL = kEncLongThreads, NS = kEncShortThreads;
-    const dim3 blocks(static_cast<uint32_t>(p.nb));
-    if (p.mode == kEncDirect) {
-        hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NL, kEncDirect>), blocks, dim3(NL), 0, s, chain, n_seg, partial, grid);
-    } else if (p.cols != kEncPerBlock) {
-        hipLaunchKernelGGL((k_enc_partials<DIM, ROWS, NS>), blocks, dim3(NS), 0, s, chain, n_seg, partial);
-        hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NS, kEncSelfSum>), blocks, dim3(NS), 0, s, chain, n_seg, partial, grid);
-    } else {
-        hipLaunchKernelGGL((k_enc_partials<DIM, ROWS, NL>), blocks, dim3(NL), 0, s, chain, n_seg, partial);
-        if (p.mode == kEncSelfSum) {
-            hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NL, kEncSelfSum>), blocks, dim3(NL), 0, s, chain, n_seg, partial, grid);
-        } else {
-            hipLaunchKernelGGL(k_enc_offsets, dim3(1), dim3(kBlock), 0, s, DIM * (ROWS - 1), p.nb, partial);
-            hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NL, kEncScanned>), blocks, dim3(NL), 0, s, chain, n_seg, partial, grid);
-        }
-    }
+void launch_encode(const float *chain, int64_t n_seg, float *grid, hipStream_t s) {
+    constexpr int NL = kEncLongThreads<ROWS>, COLS = EncGeom<DIM, ROWS, NL>::COLS;
+    if (n_seg + 1 <= kEncDirectCols)
+        hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NL, true>), dim3(static_cast<uint32_t>((n_seg + COLS) / COLS)),
+                           dim3(NL), 0, s, chain, n_seg, grid);
+    else if (n_seg + 1 <= kEncSmallCols)
+        launch_encode_blocks<DIM, ROWS, kEncShortThreads>(chain, n_seg, grid, s);
+    else
+        launch_encode_blocks<DIM, ROWS, NL>(chain, n_seg, grid, s);
 }
 
 template <int ROWS>
-void launch_encode_dim(int dim, const EncPlan &p, const float *chain, int64_t n_seg, double *partial, float *grid,
-                       hipStream_t s) {
+void launch_encode_dim(int dim, const float *chain, int64_t n_seg, float *grid, hipStream_t s) {
     switch (dim) {
-        case 1: launch_encode<1, ROWS>(p, chain, n_seg, partial, grid, s); break;
-        case 2: launch_encode<2, ROWS>(p, chain, n_seg, partial, grid, s); break;
-        case 3: launch_encode<3, ROWS>(p, chain, n_seg, partial, grid, s); break;
-        default: launch_encode<4, ROWS>(p, chain, n_seg, partial, grid, s); break;
+        case 1: launch_encode<1, ROWS>(chain, n_seg, grid, s); break;
+        case 2: launch_encode<2, ROWS>(chain, n_seg, grid, s); break;
+        case 3: launch_encode<3, ROWS>(chain, n_seg, grid, s); break;
+        default: launch_encode<4, ROWS>(chain, n_seg, grid, s); break;
     }
 }
 
-}  // namespace
-
-// Workspace of the allocation-free encoder: the block partials (one double
-// per block of kEncPerBlock columns and channel) in a file-scope device array.
-// Each device holds its own copy until the process ends; host code reaches it
-// only through the device address looked up per device below (the array's
-// name in host code is a host-side stand-in, not a device address).
-constexpr int64_t kEncScratchDoubles = int64_t(1) << 18;  // 2 MiB
-static __device__ __align__(256) double scratch[kEncScratchDoubles];
-
-namespace {
-
-// Largest chain the workspace holds: nb * dim <= kEncScratchDoubles with
-// nb = ceil((n_seg + 1) / kEncPerBlock).  (Chains of up to kEncSmallCols
-// columns take smaller blocks, at most 512 of them.)
-int64_t noalloc_max_seg(int dim) { return (kEncScratchDoubles / dim) * kEncPerBlock - 1; }
-
-constexpr int kScratchMaxDevices = 64;
-std::mutex g_scratch_mu;
-double *g_scratch_ptr[kScratchMaxDevices] = {};
-
-// Device address of the current device's scratch array, looked up once per
-// device (with that device current) and kept.
-int scratch_address(const char *fn, double **out) {
-    int dev = 0;
-    BZ_CHECK_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= kScratchMaxDevices) return fail(BZ_ERR_UNSUPPORTED, "%s: device %d", fn, dev);
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-        g_scratch_ptr[dev] = static_cast<double *>(p);
-    }
-    *out = g_scratch_ptr[dev];
-    return BZ_OK;
-}
+// Longest chain bz_encode_piecewise_noalloc takes, part of its interface.
+int64_t noalloc_max_seg(int dim) { return (int64_t(1) << 18) / dim * 2048 - 1; }
 
 }  // namespace
 }  // namespace bzi
@@ -363,33 +351,17 @@ using namespace bzi;
 
 extern "C" {
 
-// ws: caller-provided workspace of at least nb*nch doubles, or NULL for a
-// stream-ordered allocation freed after the launches (none is made for chains
-// that go in one launch).
 static int encode_chain(const char *fn, const float *chain, int64_t n_seg, int dim, int cubic, float *grid,
-                        bz_stream stream, double *ws = nullptr) {
+                        bz_stream stream) {
     if (dim < 1 || dim > kMaxDim) return fail(BZ_ERR_SHAPE, "%s: dim %d", fn, dim);
     if (n_seg < 0 || n_seg > (int64_t(1) << 40)) return fail(BZ_ERR_SHAPE, "%s: n_seg %lld", fn, (long long)n_seg);
     if (n_seg == 0) return BZ_OK;
     if (!chain || !grid) return fail(BZ_ERR_NULL, "%s: chain and grid are required", fn);
     if (!aligned(chain, 4) || !aligned(grid, 4)) return fail(BZ_ERR_ALIGN, "%s: misaligned", fn);
     const hipStream_t s = as_stream(stream);
-    const int nch = dim * (cubic ? 2 : 1);
-    const EncPlan plan = enc_plan(n_seg);
-    double *partial = ws;
-    const bool own = !ws && plan.mode != kEncDirect;
-    if (own) {
-        hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&partial), sizeof(double) * plan.nb * nch, s);
-        if (e == hipErrorOutOfMemory) return fail(BZ_ERR_NOMEM, "%s: workspace", fn);
-        BZ_CHECK_HIP(e);
-    }
-    // every partial is written by k_enc_partials before it is read: the
-    // workspace needs no clearing
-    if (cubic) launch_encode_dim<3>(dim, plan, chain, n_seg, partial, grid, s);
-    else launch_encode_dim<2>(dim, plan, chain, n_seg, partial, grid, s);
-    const hipError_t le = hipGetLastError();
-    if (own) BZ_CHECK_HIP(hipFreeAsync(partial, s));
-    if (le != hipSuccess) return hip_fail(le, fn);
+    if (cubic) launch_encode_dim<3>(dim, chain, n_seg, grid, s);
+    else launch_encode_dim<2>(dim, chain, n_seg, grid, s);
+    BZ_CHECK_LAUNCH(fn);
     return BZ_OK;
 }
 
@@ -400,14 +372,9 @@ int bz_encode_piecewise_noalloc(const float *chain, int64_t n_seg, int dim, floa
         if (n_seg < 0 || n_seg > noalloc_max_seg(dim))
             return fail(BZ_ERR_SHAPE, "%s: n_seg %lld outside 0..%lld, the workspace limit for dim %d", fn,
                         (long long)n_seg, (long long)noalloc_max_seg(dim), dim);
-        if (n_seg == 0) return BZ_OK;
-        double *ws = nullptr;
-        const int rc = scratch_address(fn, &ws);
-        if (rc) return rc;
-        return encode_chain(fn, chain, n_seg, dim, 0, grid, stream, ws);
+        return encode_chain(fn, chain, n_seg, dim, 0, grid, stream);
     });
 }
-
 
 int bz_encode_piecewise(const float *chain, int64_t n_seg, int dim, float *grid, bz_stream stream) {
     return guarded("bz_encode_piecewise",
