@@ -7,109 +7,28 @@
 // deterministic and needs no atomics.  dL/dt is per query and is written by
 // the lane that owns the query.
 #include <cmath>
-#include <vector>
 
-#include "curves_impl.h"
+#include "fit_impl.h"
 
 namespace bzi {
+
+extern template int launch_fit_run_d<1>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<2>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<3>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<4>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<5>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<6>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<7>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<8>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<9>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<10>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<11>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<12>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<13>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<14>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+extern template int launch_fit_run_d<15>(int, const FitArgs &, const FitBias &, int, hipStream_t);
+
 namespace {
-
-// Sum over the 64 lanes: a DPP butterfly inside each 16-lane row (swap
-// neighbours, swap pairs, mirror the 8-lane halves, mirror the row) leaves
-// every lane holding its row's sum; the four row sums are then read lane by
-// lane.  The result is wave-uniform.  No LDS traffic.
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-    v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
-    v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
-    v += dpp_mov<0x141>(v);  // row_half_mirror
-    v += dpp_mov<0x140>(v);  // row_mirror
-    const int b = __builtin_bit_cast(int, v);
-    return (__builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 0)) +
-            __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 16))) +
-           (__builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32)) +
-            __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48)));
-}
-
-// Sums over each 32-lane half of the wavefront (two curves per wave): the
-// same row butterfly, then rows 0+1 and rows 2+3.  Lanes get their half's sum.
-__device__ __forceinline__ float half_sum(float v) {
-    v += dpp_mov<0xB1>(v);
-    v += dpp_mov<0x4E>(v);
-    v += dpp_mov<0x141>(v);
-    v += dpp_mov<0x140>(v);
-    const int b = __builtin_bit_cast(int, v);
-    const float lo = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 0)) +
-                     __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 16));
-    const float hi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32)) +
-                     __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48));
-    return (threadIdx.x & 32) ? hi : lo;
-}
-
-// Exchange with lane ^ D inside each 32-lane half: DPP for D = 1, 2 (quad
-// permutations), ds_swizzle in xor mode (and-mask 31) for D = 4..16.
-template <int D>
-__device__ __forceinline__ float xor_lane(float v) {
-    if constexpr (D == 1) return dpp_mov<0xB1>(v);
-    else if constexpr (D == 2) return dpp_mov<0x4E>(v);
-    else return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), (D << 10) | 0x1F));
-}
-
-// Reduce-scatter over a 32-lane half: NV values per lane in, and lane l of
-// the half leaves with the half's sum of value l mod NV (NV = 16 or 32).  At
-// each exchange a lane keeps the half of its values selected by one bit of
-// its index (most significant first) and adds its partner's copy of that
-// half, so the work halves with every exchange.
-template <int NV, int D = NV / 2>
-__device__ __forceinline__ void reduce_scatter_level(float (&v)[NV], int sub) {
-    if constexpr (D >= 1) {
-        const bool hi = (sub & D) != 0;
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-            const float lo_v = v[j], hi_v = v[j + D];
-            v[j] = (hi ? hi_v : lo_v) + xor_lane<D>(hi ? lo_v : hi_v);
-        }
-        reduce_scatter_level<NV, D / 2>(v, sub);
-    }
-}
-
-template <int NV>
-__device__ __forceinline__ float reduce_scatter32(float (&v)[NV], int sub) {
-    reduce_scatter_level<NV>(v, sub);
-    float r = v[0];
-    if constexpr (NV == 16) r += xor_lane<16>(r);
-    return r;
-}
-
-// Per-curve sums of the gradient partials gb[k][i], delivered to the lane
-// that owns parameter sub = k*(D+1)+i (lanes past NP get unused values).
-// Two curves per wavefront: reduce-scatter in each half; one curve: one
-// wave sum per parameter.
-template <int D, int DIM, int CPW>
-__device__ __forceinline__ float reduce_grads(const float (&gb)[DIM][D + 1], int sub) {
-    constexpr int NP = DIM * (D + 1);
-    if constexpr (CPW == 2) {
-        constexpr int NV = NP <= 16 ? 16 : 32;
-        float v[NV];
-#pragma unroll
-        for (int e = 0; e < NV; ++e) v[e] = e < NP ? gb[e / (D + 1)][e % (D + 1)] : 0.0f;
-        return reduce_scatter32<NV>(v, sub);
-    } else {
-        float mine = 0.0f;
-#pragma unroll
-        for (int k = 0; k < DIM; ++k)
-#pragma unroll
-            for (int i = 0; i <= D; ++i) {
-                const float v = wave_sum(gb[k][i]);
-                if (sub == k * (D + 1) + i) mine = v;
-            }
-        return mine;
-    }
-}
 
 struct AdjArgs {
     const float *ctrl;
@@ -124,49 +43,6 @@ struct AdjArgs {
     int64_t plane;
     int per_object;
 };
-
-// Per query: value C, derivative C' (hodograph), and the basis B.
-template <int D, int DIM, bool RAT>
-__device__ __forceinline__ void curve_and_derivative(const float (&b)[DIM][D + 1], const float (&wv)[D + 1], float t,
-                                                     float (&B)[D + 1], float &W, float (&C)[DIM], float (&dC)[DIM]) {
-    bernstein_basis<D>(t, B);
-    float Bm[D];
-    bernstein_basis<D - 1>(t, Bm);
-    if constexpr (!RAT) {
-        W = 1.0f;
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) {
-            C[k] = dot_basis<D>(B, b[k]);
-            float d = 0.0f;
-#pragma unroll
-            for (int i = 0; i < D; ++i) d = __builtin_fmaf(b[k][i + 1] - b[k][i], Bm[i], d);
-            dC[k] = static_cast<float>(D) * d;
-        }
-    } else {
-        float wB[D + 1];
-        W = 0.0f;
-        float Wp = 0.0f;
-#pragma unroll
-        for (int i = 0; i <= D; ++i) {
-            wB[i] = wv[i] * B[i];
-            W += wB[i];
-        }
-#pragma unroll
-        for (int i = 0; i < D; ++i) Wp = __builtin_fmaf(wv[i + 1] - wv[i], Bm[i], Wp);
-        Wp *= static_cast<float>(D);
-        const float iW = 1.0f / W;
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) {
-            const float H = dot_basis<D>(wB, b[k]);
-            float Hp = 0.0f;
-#pragma unroll
-            for (int i = 0; i < D; ++i) Hp = __builtin_fmaf(wv[i + 1] * b[k][i + 1] - wv[i] * b[k][i], Bm[i], Hp);
-            Hp *= static_cast<float>(D);
-            C[k] = H * iW;
-            dC[k] = (Hp - C[k] * Wp) * iW;
-        }
-    }
-}
 
 template <int D, int DIM, bool RAT>
 __global__ __launch_bounds__(kBlock) void k_adjoint(AdjArgs a) {
@@ -225,37 +101,6 @@ __global__ __launch_bounds__(kBlock) void k_adjoint(AdjArgs a) {
     }
 }
 
-struct FitArgs {
-    float *ctrl, *t;
-    const float *y;
-    float *m_c, *v_c, *m_t, *v_t;
-    float *loss_part;
-    int64_t n_curves, n_t, plane;
-    float inv_m;        // 1 / (n_curves * n_t)
-    float lr, b1, b2, eps;
-    float ic1, ic2;  // 1 / (1 - b1^step), 1 / (1 - b2^step), rounded once from FP64
-};
-
-// Adam update with the bias corrections as multiplications by host-side
-// reciprocals and the hardware square root and reciprocal (v_sqrt_f32,
-// v_rcp_f32, about 1 ulp) instead of correctly rounded division and square
-// root sequences: the update is a heuristic step, and the IEEE sequences cost
-// a third of the fitting step's instructions.  Every rounding step is written
-// out so that all kernels produce identical bits.
-__device__ __forceinline__ float adam_c(float p, float g, float *m, float *v, const FitArgs &a, float ic1, float ic2) {
-    const float mm = __builtin_fmaf(a.b1, *m, (1.0f - a.b1) * g);
-    const float vv = __builtin_fmaf(a.b2, *v, ((1.0f - a.b2) * g) * g);
-    *m = mm;
-    *v = vv;
-    const float mh = mm * ic1, vh = vv * ic2;
-    const float upd = mh * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(vh) + a.eps);
-    return __builtin_fmaf(-a.lr, upd, p);
-}
-
-__device__ __forceinline__ float adam(float p, float g, float *m, float *v, const FitArgs &a) {
-    return adam_c(p, g, m, v, a, a.ic1, a.ic2);
-}
-
 // Fused step: L = (1/M) sum |C(t) - y|^2, gradients, Adam on t (clamped to
 // [0,1]) and on the control points.  All gradients use the parameters as they
 // were at the start of the step.  Two curves per wavefront: lanes 0-31 work
@@ -285,9 +130,13 @@ __global__ __launch_bounds__(kBlock) void k_fit_step(FitArgs a) {
     const int64_t pidx = c * NP + (sub < NP ? sub : 0);
     const float p_own = a.ctrl[pidx];
     float m_own = a.m_c[pidx], v_own = a.v_c[pidx];
+    float mine = 0.0f, loss_sum = 0.0f;
+    // blocks of kFitSpl samples per lane (see there)
+    for (int64_t j0 = 0; j0 == 0 || j0 < a.n_t; j0 += kFitSpl * L) {
+    const int64_t j1 = min(a.n_t, j0 + kFitSpl * L);
     float gb[DIM][D + 1] = {};
     float loss = 0.0f;
-    for (int64_t j = sub; live && j < a.n_t; j += L) {
+    for (int64_t j = j0 + sub; live && j < j1; j += L) {
         const int64_t q = c * a.n_t + j;
         const float t = a.t[q];
         float mt = a.m_t[q], vt = a.v_t[q];
@@ -313,8 +162,11 @@ __global__ __launch_bounds__(kBlock) void k_fit_step(FitArgs a) {
         a.v_t[q] = vt;
     }
     loss = CPW == 2 ? half_sum(loss) : wave_sum(loss);
-    if (a.loss_part && sub == 0 && live) a.loss_part[c] = loss * a.inv_m;
-    const float mine = reduce_grads<D, DIM, CPW>(gb, sub);
+    const float blk = reduce_grads<D, DIM, CPW>(gb, sub);
+    loss_sum = j0 == 0 ? loss : loss_sum + loss;
+    mine = j0 == 0 ? blk : mine + blk;
+    }
+    if (a.loss_part && sub == 0 && live) a.loss_part[c] = loss_sum * a.inv_m;
     if (sub < NP && live) {
         const float pn = adam(p_own, mine, &m_own, &v_own, a);
         a.ctrl[pidx] = pn;
@@ -387,118 +239,7 @@ __global__ __launch_bounds__(kBlock) void k_l2_adjoint(L2Args a) {
     }
 }
 
-// Many fitting steps in one launch.  Curves are optimised independently, so
-// a wavefront can keep its curves' samples, parameters and Adam moments in
-// registers across all steps: HBM is read once and written once.  Each step
-// performs exactly the arithmetic of k_fit_step, in the same order.  SPL:
-// samples per lane (n_t <= SPL * lanes per curve).  bias[step] = (ic1, ic2).
-template <int D, int DIM, int SPL>
-__global__ __launch_bounds__(kBlock) void k_fit_run(FitArgs a, const float2 *__restrict__ bias, int n_steps) {
-    constexpr int NP = DIM * (D + 1);
-    constexpr int CPW = NP <= 32 ? 2 : 1;
-    constexpr int L = 64 / CPW;
-    const int lane = threadIdx.x & 63, sub = lane % L;
-    const int64_t c0 = CPW * static_cast<int64_t>(__builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)));
-    if (c0 >= a.n_curves) return;
-    const bool has1 = CPW == 2 && c0 + 1 < a.n_curves;
-    const int64_t c = (lane < L || !has1) ? c0 : c0 + 1;
-    const bool live = lane < L || has1;
-    const int base = lane < L ? 0 : L;  // first lane of this lane's curve
-    const int64_t pidx = c * NP + (sub < NP ? sub : 0);
-    float p_own = a.ctrl[pidx], m_own = a.m_c[pidx], v_own = a.v_c[pidx];
-    float ts[SPL], mts[SPL], vts[SPL], ys[SPL][DIM];
-    int64_t qs[SPL];
-    bool ok[SPL];
-#pragma unroll
-    for (int s = 0; s < SPL; ++s) {
-        const int64_t j = sub + static_cast<int64_t>(s) * L;
-        ok[s] = live && j < a.n_t;
-        qs[s] = c * a.n_t + (ok[s] ? j : 0);
-        ts[s] = a.t[qs[s]];
-        mts[s] = a.m_t[qs[s]];
-        vts[s] = a.v_t[qs[s]];
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) ys[s][k] = a.y[k * a.plane + qs[s]];
-    }
-    float b[DIM][D + 1], wv[D + 1] = {};
-    float loss = 0.0f;
-    const float two_inv_m = 2.0f * a.inv_m;
-    for (int step = 0; step < n_steps; ++step) {
-        // current control points of this lane's curve, from the owning lanes
-        // (a lane-indexed permute through the LDS crossbar: one instruction per
-        // parameter for both curves of the wave, none of them VALU)
-        const int pb = __builtin_bit_cast(int, p_own);
-#pragma unroll
-        for (int k = 0; k < DIM; ++k)
-#pragma unroll
-            for (int i = 0; i <= D; ++i)
-                b[k][i] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((base + k * (D + 1) + i) << 2, pb));
-        const float2 bc = bias[step];
-        float gb[DIM][D + 1] = {};
-        loss = 0.0f;
-#pragma unroll
-        for (int s = 0; s < SPL; ++s) {
-            if (!ok[s]) continue;
-            float B[D + 1], W, C[DIM], dC[DIM];
-            curve_and_derivative<D, DIM, false>(b, wv, ts[s], B, W, C, dC);
-            float dt = 0.0f;
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) {
-                const float r = C[k] - ys[s][k];
-                loss = __builtin_fmaf(r, r, loss);
-                const float g = r * two_inv_m;  // = (2r) inv_m exactly: scaling by 2 commutes with rounding
-                dt = __builtin_fmaf(g, dC[k], dt);
-#pragma unroll
-                for (int i = 0; i <= D; ++i) gb[k][i] = __builtin_fmaf(g, B[i], gb[k][i]);
-            }
-            float tn = adam_c(ts[s], dt, &mts[s], &vts[s], a, bc.x, bc.y);
-            ts[s] = tn < 0.0f ? 0.0f : (tn > 1.0f ? 1.0f : tn);
-        }
-        const float mine = reduce_grads<D, DIM, CPW>(gb, sub);
-        if (sub < NP && live) p_own = adam_c(p_own, mine, &m_own, &v_own, a, bc.x, bc.y);
-    }
-    // only the last step's loss is reported, so only it is summed over the lanes
-    loss = CPW == 2 ? half_sum(loss) : wave_sum(loss);
-    if (a.loss_part && sub == 0 && live) a.loss_part[c] = loss * a.inv_m;
-    if (sub < NP && live) {
-        a.ctrl[pidx] = p_own;
-        a.m_c[pidx] = m_own;
-        a.v_c[pidx] = v_own;
-    }
-#pragma unroll
-    for (int s = 0; s < SPL; ++s)
-        if (ok[s]) {
-            a.t[qs[s]] = ts[s];
-            a.m_t[qs[s]] = mts[s];
-            a.v_t[qs[s]] = vts[s];
-        }
-}
-
-template <int D, int DIM>
-int launch_fit_run_dd(const FitArgs &a, const float2 *bias, int n_steps, hipStream_t s) {
-    constexpr int NP = DIM * (D + 1);
-    constexpr int L = NP <= 32 ? 32 : 64;
-    constexpr int CPW = 64 / L;
-    const uint32_t blocks = static_cast<uint32_t>((a.n_curves + 4 * CPW - 1) / (4 * CPW));
-    const int64_t spl = (a.n_t + L - 1) / L;
-    if (spl <= 1) hipLaunchKernelGGL((k_fit_run<D, DIM, 1>), dim3(blocks), dim3(kBlock), 0, s, a, bias, n_steps);
-    else if (spl <= 2) hipLaunchKernelGGL((k_fit_run<D, DIM, 2>), dim3(blocks), dim3(kBlock), 0, s, a, bias, n_steps);
-    else hipLaunchKernelGGL((k_fit_run<D, DIM, 4>), dim3(blocks), dim3(kBlock), 0, s, a, bias, n_steps);
-    BZ_CHECK_LAUNCH("k_fit_run");
-    return BZ_OK;
-}
-
-template <int D>
-int launch_fit_run_d(int dim, const FitArgs &a, const float2 *bias, int n_steps, hipStream_t s) {
-    switch (dim) {
-        case 1: return launch_fit_run_dd<D, 1>(a, bias, n_steps, s);
-        case 2: return launch_fit_run_dd<D, 2>(a, bias, n_steps, s);
-        case 3: return launch_fit_run_dd<D, 3>(a, bias, n_steps, s);
-        default: return launch_fit_run_dd<D, 4>(a, bias, n_steps, s);
-    }
-}
-
-int launch_fit_run(int degree, int dim, const FitArgs &a, const float2 *bias, int n_steps, hipStream_t s) {
+int launch_fit_run(int degree, int dim, const FitArgs &a, const FitBias &bias, int n_steps, hipStream_t s) {
     switch (degree) {
         case 1: return launch_fit_run_d<1>(dim, a, bias, n_steps, s);
         case 2: return launch_fit_run_d<2>(dim, a, bias, n_steps, s);
@@ -737,57 +478,19 @@ int bz_fit_adam_run(float *ctrl, float *t, const float *y, int64_t n_curves, int
         if (rc || n_curves == 0 || n_t == 0 || n_steps == 0) return rc;
         if (first_step < 1 || n_steps < 0) return fail(BZ_ERR_SHAPE, "%s: steps count from 1", fn);
         const hipStream_t s = as_stream(stream);
-        const int64_t lanes_per_curve = dim * (degree + 1) <= 32 ? 32 : 64;
-        if (n_t <= 4 * lanes_per_curve) {
-            // all steps in one launch, per-curve state in registers
-            std::vector<float> tab(2 * static_cast<size_t>(n_steps));
-            for (int i = 0; i < n_steps; ++i) {
-                const FitArgs ai = make_fit_args(ctrl, t, y, n_curves, n_t, m_ctrl, v_ctrl, m_t, v_t, first_step + i,
+        for (int i0 = 0; i0 < n_steps && rc == BZ_OK; i0 += kFitStepsPerLaunch) {
+            const int n = std::min(kFitStepsPerLaunch, n_steps - i0);
+            FitBias bias;
+            for (int i = 0; i < n; ++i) {
+                const FitArgs ai = make_fit_args(ctrl, t, y, n_curves, n_t, m_ctrl, v_ctrl, m_t, v_t, first_step + i0 + i,
                                                  lr, beta1, beta2, eps, loss_part);
-                tab[2 * i] = ai.ic1;
-                tab[2 * i + 1] = ai.ic2;
+                bias.v[i] = make_float2(ai.ic1, ai.ic2);
             }
-            float2 *bias = nullptr;
-            hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&bias), tab.size() * sizeof(float), s);
-            if (e == hipErrorOutOfMemory) return fail(BZ_ERR_NOMEM, "%s: bias table", fn);
-            BZ_CHECK_HIP(e);
-            e = hipMemcpyAsync(bias, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice, s);
-            const FitArgs a = make_fit_args(ctrl, t, y, n_curves, n_t, m_ctrl, v_ctrl, m_t, v_t, first_step, lr, beta1,
-                                            beta2, eps, loss_part);
-            if (e == hipSuccess) rc = launch_fit_run(degree, dim, a, bias, n_steps, s);
-            else rc = hip_fail(e, "bias table copy");
-            const hipError_t e2 = hipFreeAsync(bias, s);
-            const hipError_t e3 = hipStreamSynchronize(s);
-            if (rc == BZ_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipFreeAsync");
-            if (rc == BZ_OK && e3 != hipSuccess) rc = hip_fail(e3, "hipStreamSynchronize");
-            return rc;
+            const FitArgs a = make_fit_args(ctrl, t, y, n_curves, n_t, m_ctrl, v_ctrl, m_t, v_t, first_step + i0, lr,
+                                            beta1, beta2, eps, loss_part);
+            rc = launch_fit_run(degree, dim, a, bias, n, s);
         }
-        // otherwise: capture the single steps on a private stream and replay the graph
-        hipStream_t cap;
-        BZ_CHECK_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-        hipGraph_t graph = nullptr;
-        hipGraphExec_t exec = nullptr;
-        hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
-            for (int i = 0; i < n_steps && rc == BZ_OK; ++i) {
-                const FitArgs a = make_fit_args(ctrl, t, y, n_curves, n_t, m_ctrl, v_ctrl, m_t, v_t, first_step + i,
-                                                lr, beta1, beta2, eps, loss_part);
-                rc = launch_fit(degree, dim, a, cap);
-            }
-            const hipError_t e2 = hipStreamEndCapture(cap, &graph);
-            if (rc == BZ_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipStreamEndCapture");
-        } else {
-            rc = hip_fail(e, "begin capture");
-        }
-        if (rc == BZ_OK) {
-            e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-            if (e == hipSuccess) e = hipGraphLaunch(exec, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);
-            if (e != hipSuccess) rc = hip_fail(e, "graph launch");
-        }
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
-        (void)hipStreamDestroy(cap);
+        if (rc == BZ_OK) BZ_CHECK_HIP(hipStreamSynchronize(s));
         return rc;
     });
 }
