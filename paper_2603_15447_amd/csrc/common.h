@@ -96,6 +96,11 @@ constexpr float binomf(int n, int k) {
 }
 
 __device__ __forceinline__ void st_stream(float *p, float v) { __builtin_nontemporal_store(v, p); }
+// Store at a wave-uniform base plus a lane's offset in floats (below 2^30): the
+// base stays in scalar registers and the lane needs no 64-bit address.
+__device__ __forceinline__ float *at_lane(float *base, uint32_t i) {
+    return reinterpret_cast<float *>(reinterpret_cast<char *>(base) + static_cast<size_t>(4u * i));
+}
 __device__ __forceinline__ float ld_stream(const float *p) { return __builtin_nontemporal_load(p); }
 
 }  // namespace bzi

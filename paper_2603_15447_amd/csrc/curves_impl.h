@@ -1,11 +1,12 @@
 // Curve evaluation kernels (integral and rational Bezier curves) for gfx950.
 //
-// One thread evaluates one (curve, parameter) query; query q = c*n_t + j,
-// so a wavefront covers 64 consecutive parameters of one curve whenever
-// n_t >= 64 and the control-point loads of the wave hit one or two cache
-// lines.  Control points are held in registers, the evaluation form is
+// Query q = c*n_t + j is one (curve, parameter) pair; the evaluation form is
 // unrolled at compile time for each degree 1..15 and dimension 1..4, and
 // results go out with non-temporal stores to the planar out[dim][n*n_t].
+//  k_curves        one query per thread, its curve's control points loaded for
+//                  it: by scalar loads where a wavefront stays on one curve.
+//  k_curves_mixed  a workgroup stages the control points of its curves in LDS,
+//                  ready for the form.
 #pragma once
 
 #include "common.h"
@@ -128,32 +129,66 @@ __device__ __forceinline__ void eval_channels(const float (&b)[CH][D + 1], float
 }
 
 // FP64 de Casteljau on homogeneous points, used to re-evaluate rational
-// points whose weight sum is ill-conditioned in FP32.
+// points whose weight sum is ill-conditioned in FP32.  Inlined where it is
+// used, once per kernel, and holding one row at a time: as a function of its
+// own, its registers and the call's held every rational kernel at five waves
+// per SIMD.
 template <int D, int DIM, typename T>
-__device__ __attribute__((noinline)) void rational_fp64(const T *__restrict__ ctrl, const T *__restrict__ w, uint32_t c,
-                                                        float t, float (&res)[DIM]) {
+__device__ __forceinline__ void rational_fp64(const T *__restrict__ ctrl, const T *__restrict__ w, uint32_t c, float t,
+                                              float (&res)[DIM]) {
     const double td = static_cast<double>(t);
-    double ww[D + 1];
-#pragma unroll
-    for (int i = 0; i <= D; ++i) ww[i] = static_cast<double>(to_f32<T>(w[static_cast<size_t>(c) * (D + 1) + i]));
-    double W[D + 1];
-#pragma unroll
-    for (int i = 0; i <= D; ++i) W[i] = ww[i];
-#pragma unroll
-    for (int lvl = 1; lvl <= D; ++lvl)
-#pragma unroll
-        for (int i = 0; i <= D - lvl; ++i) W[i] = lerp(W[i], W[i + 1], td);
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
+    const T *__restrict__ Wp = w + static_cast<size_t>(c) * (D + 1);
+    double W = 0.0;
+#pragma unroll 1
+    for (int k = 0; k <= DIM; ++k) {  // the weight, then the coordinates
+        const T *__restrict__ Pk = ctrl + (static_cast<size_t>(c) * DIM + (k > 0 ? k - 1 : 0)) * (D + 1);
         double H[D + 1];
 #pragma unroll
-        for (int i = 0; i <= D; ++i)
-            H[i] = ww[i] * static_cast<double>(to_f32<T>(ctrl[(static_cast<size_t>(c) * DIM + k) * (D + 1) + i]));
+        for (int i = 0; i <= D; ++i) {
+            const double wi = static_cast<double>(to_f32<T>(Wp[i]));
+            H[i] = k > 0 ? wi * static_cast<double>(to_f32<T>(Pk[i])) : wi;
+        }
 #pragma unroll
         for (int lvl = 1; lvl <= D; ++lvl)
 #pragma unroll
             for (int i = 0; i <= D - lvl; ++i) H[i] = lerp(H[i], H[i + 1], td);
-        res[k] = static_cast<float>(H[0] / W[0]);
+        if (k == 0) W = H[0];
+#pragma unroll
+        for (int e = 0; e < DIM; ++e) res[e] = k == e + 1 ? static_cast<float>(H[0] / W) : res[e];
+    }
+}
+
+// r[k] / W of all coordinates, correctly rounded: one reciprocal for all of
+// them, refined once, and per coordinate a quotient with one residual
+// correction (4 instructions against 11 of a division of its own).  Valid
+// while no step under- or overflows; otherwise the plain divisions.
+template <int DIM, int CH>
+__device__ __forceinline__ void divide_all(const float (&r)[CH], float W, float (&res)[DIM]) {
+    constexpr uint32_t kLo = (127u - 40u) << 23, kHi = (127u + 40u) << 23;  // 2^-40, 2^40
+    float big = 0.0f;
+    uint32_t small = 0xffffffffu;
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        const uint32_t u = __float_as_uint(__builtin_fabsf(r[k]));
+        big = __builtin_fmaxf(big, __builtin_fabsf(r[k]));
+        small = min(small, u - 1u);  // zero passes
+    }
+    const uint32_t uw = __float_as_uint(__builtin_fabsf(W));
+    const bool plain = !(uw >= kLo && uw <= kHi && __float_as_uint(big) <= kHi && small >= kLo);
+    bool nan = false;  // (fmax drops a NaN)
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) nan = nan || r[k] != r[k];
+    if (plain || nan) {
+#pragma unroll
+        for (int k = 0; k < DIM; ++k) res[k] = r[k] / W;
+        return;
+    }
+    float y = __builtin_amdgcn_rcpf(W);
+    y = __builtin_fmaf(__builtin_fmaf(-W, y, 1.0f), y, y);
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        const float q = r[k] * y;
+        res[k] = __builtin_copysignf(__builtin_fmaf(__builtin_fmaf(-W, q, r[k]), y, q), q);
     }
 }
 
@@ -170,6 +205,9 @@ struct CurveArgs {
     int per_object;        // t[n][n_t] vs t[n_t]
     float kappa;           // rational conditioning threshold (<= 0: off)
     uint32_t *n_fixed;     // nullable device counter
+    // k_curves_mixed: queries per workgroup, curves it may touch, and whether the
+    // planes lie alike to the 64-byte lines
+    int chunk, slots, same;
 };
 
 // UNI: n_t is a multiple of 64, so each wavefront evaluates one curve; its
@@ -224,8 +262,7 @@ __global__ __launch_bounds__(kBlock) void k_curves(CurveArgs a) {
         if (fix) {
             rational_fp64<D, DIM, T>(static_cast<const T *>(a.ctrl), static_cast<const T *>(a.w), cl, t, res);
         } else {
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) res[k] = r[k] / W;
+            divide_all<DIM>(r, W, res);
         }
         if (a.n_fixed) {
             const uint64_t m = __ballot(fix);
@@ -234,6 +271,151 @@ __global__ __launch_bounds__(kBlock) void k_curves(CurveArgs a) {
         }
 #pragma unroll
         for (int k = 0; k < DIM; ++k) st_stream(a.out + k * a.plane + qg, res[k]);
+    }
+}
+
+// A workgroup takes `chunk` consecutive queries, stages the control points of
+// the curves they lie on in LDS -- widened, times their weights, or as Seiler
+// terms, once per curve instead of once per query -- and evaluates up to four
+// queries per thread from there.  Loading a curve per query took a vector load
+// and a conversion per coefficient.
+// The stores bypass the caches and want whole lines, so a chunk begins on one;
+// where the coordinate planes don't lie alike (their distance is no multiple of
+// 64 bytes) each plane takes its own part of the chunk, up to 31 queries apart,
+// by way of LDS.
+template <int D, int DIM, bool RAT>
+struct MixedGeom {
+    static constexpr int CH = DIM + (RAT ? 1 : 0);
+    static constexpr int PAD = (D + 4) / 4 * 4;     // floats per row: whole 16-byte vectors
+    static constexpr int CURVE = CH * PAD + 4;      // per curve; the last four: all weights positive
+};
+
+// Floats of a query's store past the last 128-byte line.
+__device__ __forceinline__ uint32_t line_offset(const float *p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p) >> 2) & 31u;
+}
+
+template <int D, int DIM, int F, bool RAT, typename T>
+__global__ __launch_bounds__(kBlock) void k_curves_mixed(CurveArgs a) {
+    using G = MixedGeom<D, DIM, RAT>;
+    constexpr int CH = G::CH, PAD = G::PAD;
+    extern __shared__ __align__(16) float lds[];
+    float *__restrict__ out = a.out + a.q0;
+    const uint32_t at = blockIdx.x * a.chunk;
+    const uint32_t sh = a.same ? line_offset(out) : 31u;
+    const uint32_t first = at > sh ? at - sh : 0;
+    const uint32_t end = min(a.nq, at + a.chunk - (a.same ? sh : 0u));
+    const int n = static_cast<int>(end - first);
+    if (n <= 0) return;
+    const uint32_t c_lo = fdiv(first, a.div_nt), s0 = first - c_lo * a.div_nt.d;
+    const int n_c = static_cast<int>(fdiv(s0 + n - 1, a.div_nt)) + 1;
+    const float *__restrict__ tq = a.per_object ? a.t + a.q0 + first : a.t;
+    // parameter of query first + p (of the last one beyond), and its curve
+    auto param = [&](int p, uint32_t &k) {
+        const uint32_t q = min(p, n - 1);
+        k = fdiv(s0 + q, a.div_nt);
+        return tq[a.per_object ? q : s0 + q - k * a.div_nt.d];
+    };
+    uint32_t k_next;
+    float t_next = param(threadIdx.x, k_next);  // on its way while the curves are staged
+    const T *__restrict__ P = static_cast<const T *>(a.ctrl) + static_cast<size_t>(c_lo) * DIM * (D + 1);
+    const T *__restrict__ Wp = RAT ? static_cast<const T *>(a.w) + static_cast<size_t>(c_lo) * (D + 1) : nullptr;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < n_c * DIM * (D + 1); e += kBlock) {
+        const int r = e / (D + 1), i = e - r * (D + 1);
+        const int k = r / DIM, ch = r - k * DIM;
+        float v = to_f32<T>(P[e]);
+        if constexpr (RAT) v *= to_f32<T>(Wp[k * (D + 1) + i]);
+        lds[k * G::CURVE + ch * PAD + i] = v;
+    }
+    if constexpr (RAT) {
+#pragma unroll 2
+        for (int e = threadIdx.x; e < n_c * (D + 1); e += kBlock) {
+            const int k = e / (D + 1), i = e - k * (D + 1);
+            lds[k * G::CURVE + DIM * PAD + i] = to_f32<T>(Wp[e]);
+        }
+        for (int k = kBlock - 1 - threadIdx.x; k < n_c; k += kBlock) {
+            bool allpos = true;
+#pragma unroll
+            for (int i = 0; i <= D; ++i) allpos = allpos && (to_f32<T>(Wp[k * (D + 1) + i]) > 0.0f);
+            lds[k * G::CURVE + CH * PAD] = allpos ? 1.0f : 0.0f;
+        }
+    }
+    __syncthreads();
+    if constexpr (F == FORM_SEILER) {
+        for (int r = threadIdx.x; r < n_c * CH; r += kBlock) {
+            float *row = lds + (r / CH) * G::CURVE + (r % CH) * PAD;
+            float b[D + 1], sc[D + 1];
+#pragma unroll
+            for (int i = 0; i <= D; ++i) b[i] = row[i];
+            seiler_terms<D, float>(b, sc);
+#pragma unroll
+            for (int i = 0; i <= D; ++i) row[i] = sc[i];
+        }
+        __syncthreads();
+    }
+    constexpr int FE = F == FORM_SEILER ? FORM_SEILER_PRE : F;  // from the staged data
+    float *__restrict__ buf = lds + a.slots * G::CURVE;         // [DIM][chunk + 32] unless the planes lie alike
+    const int pitch = a.chunk + 32;
+    auto points = [&](auto same) {
+#pragma unroll 1
+        for (int p = threadIdx.x; p < n; p += kBlock) {
+            const float t = t_next;
+            const uint32_t kq = k_next;
+            t_next = param(p + kBlock, k_next);
+            const float *__restrict__ row = lds + kq * G::CURVE;
+            float b[CH][D + 1], r[CH], res[DIM];
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+#pragma unroll
+                for (int e = 0; e <= D; ++e) b[k][e] = row[k * PAD + e];
+            eval_channels<D, CH, FE>(b, t, r);
+            if constexpr (!RAT) {
+#pragma unroll
+                for (int k = 0; k < DIM; ++k) res[k] = r[k];
+            } else {
+                const float W = r[DIM];
+                const uint32_t cl = c_lo + kq;
+                bool fix = false;
+                if (a.kappa > 0.0f && !(row[CH * PAD] != 0.0f && W > 0.0f && W < __builtin_inff())) {
+                    float aw[1][D + 1], A[1];
+#pragma unroll
+                    for (int e = 0; e <= D; ++e)
+                        aw[0][e] = __builtin_fabsf(to_f32<T>(static_cast<const T *>(a.w)[static_cast<size_t>(cl) * (D + 1) + e]));
+                    eval_channels<D, 1, F>(aw, t, A);
+                    fix = (t == t) && !(A[0] <= a.kappa * __builtin_fabsf(W));
+                }
+                if (fix) rational_fp64<D, DIM, T>(static_cast<const T *>(a.ctrl), static_cast<const T *>(a.w), cl, t, res);
+                else divide_all<DIM>(r, W, res);
+                if (a.n_fixed) {
+                    // (queries before `at` are the previous workgroup's to count)
+                    const uint64_t m = __ballot(fix && (decltype(same)::value || first + p >= at));
+                    if (m != 0 && __lane_id() == static_cast<unsigned>(__ffsll(static_cast<long long>(m)) - 1))
+                        atomicAdd(a.n_fixed, static_cast<uint32_t>(__popcll(m)));
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < DIM; ++k) {
+                if constexpr (decltype(same)::value) st_stream(at_lane(out + k * a.plane + first, p), res[k]);
+                else buf[k * pitch + p] = res[k];
+            }
+        }
+    };
+    if (a.same) {
+        points(std::true_type{});
+        return;
+    }
+    points(std::false_type{});
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        float *__restrict__ oc = out + k * a.plane;
+        const uint32_t sc = line_offset(oc), lo = at > sc ? 0 : sc - at;  // plane queries [at - sc + lo, ...)
+        const uint32_t n_own = min(static_cast<uint32_t>(a.chunk), a.nq + sc - at);
+        float *__restrict__ to = oc + at - sc;
+        const float *__restrict__ from = buf + k * pitch + static_cast<int>(at - sc - first);
+        for (uint32_t p = threadIdx.x; p < n_own; p += kBlock)
+            if (p >= lo) st_stream(at_lane(to, p), from[p]);
     }
 }
 
@@ -251,24 +433,56 @@ __global__ __launch_bounds__(kBlock) void k_to_seiler(const T *__restrict__ ctrl
 }
 
 // ---------------------------------------------------------------- host
-template <int F, bool RAT, typename T, int D, bool UNI>
-int launch_curves_du(int dim, const CurveArgs &a, hipStream_t s) {
-    const uint32_t blocks = (a.nq + kBlock - 1) / kBlock;
-    switch (dim) {
-        case 1: hipLaunchKernelGGL((k_curves<D, 1, F, RAT, T, UNI>), dim3(blocks), dim3(kBlock), 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_curves<D, 2, F, RAT, T, UNI>), dim3(blocks), dim3(kBlock), 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_curves<D, 3, F, RAT, T, UNI>), dim3(blocks), dim3(kBlock), 0, s, a); break;
-        case 4: hipLaunchKernelGGL((k_curves<D, 4, F, RAT, T, UNI>), dim3(blocks), dim3(kBlock), 0, s, a); break;
-        default: return fail(BZ_ERR_SHAPE, "dim %d out of range", dim);
+// Which kernel: integral points of curves with n_t a multiple of 64 come from
+// scalar-loaded control points (staging them in LDS: 10.0 against 9.7 us for
+// 16384 cubics x 256), except in Seiler form, whose terms are then formed once
+// per curve (degree 7: 12.6 against 18.1 us).  Curves of fewer than
+// kMixedMinT queries are loaded per query: so many would be staged per workgroup
+// that it gets few of them (3,000,000 cubics x 1: 30 against 36 us).
+// Everything else is staged (40009 bf16 curves of degree 9 in 4D x 100: 17 us,
+// 20 per query).
+constexpr uint32_t kMixedMinT = 8;
+
+template <int F, bool RAT, typename T, int D, int DIM>
+void launch_curves_dd(CurveArgs a, hipStream_t s) {
+    const uint32_t n_t = a.div_nt.d, flat = (a.nq + kBlock - 1) / kBlock;
+    if constexpr (!RAT && F != FORM_SEILER) {
+        if (n_t % 64 == 0) {
+            hipLaunchKernelGGL((k_curves<D, DIM, F, RAT, T, true>), dim3(flat), dim3(kBlock), 0, s, a);
+            return;
+        }
     }
-    BZ_CHECK_LAUNCH("k_curves");
-    return BZ_OK;
+    if (n_t < kMixedMinT) {
+        hipLaunchKernelGGL((k_curves<D, DIM, F, RAT, T, false>), dim3(flat), dim3(kBlock), 0, s, a);
+        return;
+    }
+    // chunks of 1024 queries, fewer in calls too small to give every CU two
+    // workgroups and where the curves of so many would not leave a CU four
+    using G = MixedGeom<D, DIM, RAT>;
+    a.same = DIM == 1 || a.plane % 16 == 0;
+    size_t floats = 0;
+    for (int want = a.nq >= 1024u * 512 ? 1024 : a.nq >= 512u * 512 ? 512 : 256;; want /= 2) {
+        a.chunk = a.same ? want : want - 32;  // with the planes' own first queries: whole threads
+        const uint32_t span = a.chunk + (a.same ? 0 : 31);
+        a.slots = static_cast<int>((span + n_t - 2) / n_t + 1);
+        floats = static_cast<size_t>(a.slots) * G::CURVE + (a.same ? 0 : DIM * (a.chunk + 32));
+        if (floats <= 10240 || want == 128) break;
+    }
+    const uint32_t blocks = static_cast<uint32_t>((static_cast<uint64_t>(a.nq) + 31 + a.chunk - 1) / a.chunk);
+    hipLaunchKernelGGL((k_curves_mixed<D, DIM, F, RAT, T>), dim3(blocks), dim3(kBlock), floats * sizeof(float), s, a);
 }
 
 template <int F, bool RAT, typename T, int D>
 int launch_curves_d(int dim, const CurveArgs &a, hipStream_t s) {
-    if (a.div_nt.d % 64 == 0) return launch_curves_du<F, RAT, T, D, true>(dim, a, s);
-    return launch_curves_du<F, RAT, T, D, false>(dim, a, s);
+    switch (dim) {
+        case 1: launch_curves_dd<F, RAT, T, D, 1>(a, s); break;
+        case 2: launch_curves_dd<F, RAT, T, D, 2>(a, s); break;
+        case 3: launch_curves_dd<F, RAT, T, D, 3>(a, s); break;
+        case 4: launch_curves_dd<F, RAT, T, D, 4>(a, s); break;
+        default: return fail(BZ_ERR_SHAPE, "dim %d out of range", dim);
+    }
+    BZ_CHECK_LAUNCH("k_curves");
+    return BZ_OK;
 }
 
 // Launch one chunk of curve queries for form F (rational when RAT) with

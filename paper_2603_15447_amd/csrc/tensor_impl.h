@@ -72,11 +72,6 @@ struct GridArgs {
     int same;               // whole sequence: the planes lie alike to the 64-byte lines
 };
 
-// Points of the sequence that a plane's store at p is past the last 128-byte line.
-__device__ __forceinline__ uint32_t line_offset(const float *p) {
-    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p) >> 2) & 31u;
-}
-
 // Floats of one (coordinate, column) or row entry of the LDS tables.
 template <int DU>
 constexpr int kGridPad = (DU + 4) / 4 * 4;
@@ -197,13 +192,14 @@ __global__ __launch_bounds__(kBlock) void k_tensor_grid(const T *__restrict__ ct
     float *__restrict__ buf = tab_r + PAD * DIM * n_cols;  // [DIM][chunk + 32]
     const int pitch = g.chunk + 32;
     // every point of the chunk; a full chunk's four per thread without bounds
-    // checks between them, so that their LDS reads overlap
+    // checks between them, so that their LDS reads overlap (the one point too
+    // many of a relayed chunk is its last again)
     auto each = [&](auto f) {
-        if (n == 4 * kBlock) {
+        if (n >= 4 * kBlock - 1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) f(i);
+            for (int i = 0; i < 4; ++i) f(min(static_cast<int>(threadIdx.x) + i * kBlock, n - 1));
         } else {
-            for (int i = 0; static_cast<int>(threadIdx.x) + i * kBlock < n; ++i) f(i);
+            for (int p = threadIdx.x; p < n; p += kBlock) f(p);
         }
     };
     auto points = [&](auto same) {
@@ -221,16 +217,21 @@ __global__ __launch_bounds__(kBlock) void k_tensor_grid(const T *__restrict__ ct
             for (int c = 0; c < DIM; ++c)
 #pragma unroll
                 for (int i = 0; i <= DU; ++i) R[c][i] = tab_r[(c * n_cols + b) * PAD + i];
-            each([&](int i) {
+            auto step_to = [&](int i) {
                 float Bu[DU + 1];
                 row(a + i * step, Bu);
 #pragma unroll
                 for (int c = 0; c < DIM; ++c) put(c, threadIdx.x + i * kBlock, dot_basis<DU>(Bu, R[c]));
-            });
+            };
+            if (n == 4 * kBlock) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) step_to(i);
+            } else {
+                for (int i = 0; static_cast<int>(threadIdx.x) + i * kBlock < n; ++i) step_to(i);
+            }
             return;
         }
-        each([&](int i) {
-            const int p = threadIdx.x + i * kBlock;
+        each([&](int p) {
             const uint32_t k = fdiv(s0 + p, g.div_npts), r = s0 + p - k * g.npts;
             const uint32_t a = fdiv(r, g.div_cb), b = r - a * g.cb;
             float Bu[DU + 1];

@@ -1,0 +1,73 @@
+"""GPU: curves staged per workgroup -- chunk edges, chunks over many and over
+parts of curves, planes that do and don't lie alike to the 64-byte lines,
+outputs off a cache line, the switch to per-query loading below 8 parameters --
+against the FP64 oracle, and the count of recomputed rational points."""
+import numpy as np
+import pytest
+import torch
+
+import bz_synth
+import paper_2603_15447_amd as bz
+from tests._gpu import TOL_F32, bbox_err, extents, host, to_dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 7), (1, 8), (3, 33), (31, 33), (32, 33), (1000, 9), (1001, 63), (524, 1001), (20001, 27), (5242, 100),
+          (8191, 65), (16400, 33), (2, 2047)]
+
+
+@pytest.mark.parametrize("n,nt", SHAPES)
+@pytest.mark.parametrize("degree,dim", [(3, 3), (15, 4), (4, 1)])
+def test_integral(orc, n, nt, degree, dim):
+    ctrl, t = bz_synth.random_curves(n, degree, dim, nt, seed=n + nt + degree)
+    ref = orc.bezier_decasteljau(ctrl, t, per_object=True)
+    cd, td = to_dev(ctrl), to_dev(t)
+    for m in ("decasteljau", "bernstein", "seiler"):
+        assert bbox_err(host(bz.eval_bezier(cd, td, m)), ref, extents(ctrl), nt) <= TOL_F32, m
+    sc = bz.bezier_to_seiler(cd)
+    assert bbox_err(host(bz.eval_seiler(sc, td)), ref, extents(ctrl), nt) <= TOL_F32
+    # shared parameters, and an output that starts off a cache line
+    flat = torch.full((dim * n * nt + 5,), float("nan"), device=cd.device)
+    got = bz.eval_bezier(cd, td[0].contiguous(), "bernstein", out=flat[5:].view(dim, n * nt))
+    ref = orc.bezier_decasteljau(ctrl, t[0])
+    assert bbox_err(host(got), ref, extents(ctrl), nt) <= TOL_F32
+    assert torch.isnan(flat[:5]).all()
+
+
+@pytest.mark.parametrize("n,nt", [(3, 64), (31, 33), (1000, 9), (5242, 100), (524, 1001)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+def test_rational(orc, n, nt, dtype):
+    ctrl, w, t = bz_synth.rational_curves(n, 5, 3, nt, seed=n + nt)
+    cd, wd, td = to_dev(ctrl).to(dtype), to_dev(w).to(dtype), to_dev(t)
+    c, wr = cd.float().cpu().numpy(), wd.float().cpu().numpy()
+    ref = orc.rational_eval(c, wr, t, per_object=True)
+    for m in ("decasteljau", "bernstein", "seiler"):
+        assert bbox_err(host(bz.eval_rational(cd, wd, td, m)), ref, extents(c), nt) <= TOL_F32, m
+
+
+@pytest.mark.parametrize("n,nt", [(40, 33), (5242, 100), (16400, 33)])
+def test_recomputed_points_are_counted_once(n, nt):
+    """Weights w, -w, w cancel at t = 1/2 exactly: each such query is
+    recomputed, and counted by one workgroup only."""
+    ctrl = torch.rand((n, 3, 3), device="cuda")
+    w = torch.tensor([1.0, -1.0, 1.0], device="cuda").repeat(n, 1)
+    t = torch.full((n, nt), 0.125, device="cuda")
+    t[:, ::3] = 0.5  # 1/4 - 1/2 + 1/4 = 0: conditioning number infinite
+    cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+    bz.eval_rational(ctrl, w, t, "bernstein", n_fixed=cnt)
+    assert int(cnt) == n * len(range(0, nt, 3))
+
+
+def test_division_ranges(orc):
+    """The shared reciprocal and its fallback: weight sums and products from
+    the denormals to near overflow, zero and negative zero coordinates."""
+    n, nt = 64, 33
+    rng = np.random.default_rng(5)
+    ctrl = rng.uniform(-1, 1, (n, 3, 2)).astype(np.float32)
+    ctrl[:, 2] = 0.0
+    ctrl[::2, 1] = -0.0
+    ctrl *= np.exp2(rng.integers(-30, 31, (n, 1, 1))).astype(np.float32)
+    w = np.exp2(rng.integers(-90, 91, (n, 1)) + rng.uniform(-1, 1, (n, 2))).astype(np.float32)
+    t = rng.random((n, nt)).astype(np.float32)
+    got = host(bz.eval_rational(to_dev(ctrl), to_dev(w), to_dev(t), "bernstein"))
+    assert bbox_err(got, orc.rational_eval(ctrl, w, t, per_object=True), extents(ctrl), nt) <= TOL_F32
