@@ -136,8 +136,14 @@ def _ptr(x):
     return x.data_ptr()
 
 
+# The current device's current stream as a handle: torch.cuda.current_stream()
+# builds a Stream object for it, 2.7 us of a small call's 9.6.
+_current_device = torch._C._cuda_getDevice
+_current_stream = torch._C._cuda_getCurrentRawStream
+
+
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return _current_stream(_current_device())
 
 
 def _dtype(x):
