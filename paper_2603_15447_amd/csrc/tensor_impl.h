@@ -9,6 +9,8 @@
 //                  then du+1 FMAs per coordinate and point.
 //  k_tensor_points one object per wavefront, random (u,v[,w]) per query,
 //                  4 queries per lane, separable contraction w -> v -> u.
+//  k_tensor_points_mfma  volumes of degrees 2 and 3 likewise, w contracted on the
+//                  matrix cores.
 #pragma once
 #include "curves_impl.h"
 
@@ -313,22 +315,29 @@ GridArgs grid_args(int nu, int nv, int64_t n_obj, int64_t plane) {
 }
 
 // ------------------------------------------------------------------ VALU points
-// One wavefront per object, 4 queries per lane at a time: the object's
+// One object per wavefront, 4 queries per lane at a time: the object's
 // control points are wave-uniform (scalar loads into SGPRs) and each one
-// feeds the FMAs of 4 queries.  Separable contraction w -> v -> u.
+// feeds the FMAs of 4 queries.  Separable contraction w -> v -> u.  An
+// object's queries go to waves_per_obj wavefronts, of per_wave * 64 * kPtsQ each.
+// (Two queries per lane for objects of up to 128: 31 us for 30000 bicubics x 65,
+// against 23.5 with four, half of them idle.)
 constexpr int kPtsQ = 4;
 
 template <int DU, int DV, int DW, int DIM, typename T, int BASIS>
 __global__ __launch_bounds__(kBlock) void k_tensor_points(const T *__restrict__ ctrl, const float *__restrict__ uvw,
-                                                          int64_t n_per, uint32_t n_obj, float *__restrict__ out,
-                                                          int64_t plane, int64_t o0) {
+                                                          int64_t n_per, uint32_t n_obj, uint32_t waves_per_obj,
+                                                          int per_wave, float *__restrict__ out, int64_t plane,
+                                                          int64_t o0) {
     constexpr int NCP = (DU + 1) * (DV + 1) * (DW + 1);
     constexpr int NPAR = DW > 0 ? 3 : 2;
-    const uint32_t o = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
+    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
+    const uint32_t o = w / waves_per_obj;
     if (o >= n_obj) return;
     const int lane = threadIdx.x & 63;
     const T *__restrict__ P = ctrl + static_cast<size_t>(o) * DIM * NCP;
-    for (int64_t j0 = 0; j0 < n_per; j0 += 64 * kPtsQ) {
+    const int64_t j_begin = static_cast<int64_t>(w - o * waves_per_obj) * per_wave * (64 * kPtsQ);
+    const int64_t j_end = min(n_per, j_begin + static_cast<int64_t>(per_wave) * (64 * kPtsQ));
+    for (int64_t j0 = j_begin; j0 < j_end; j0 += 64 * kPtsQ) {
         float Bu[kPtsQ][DU + 1], Bv[kPtsQ][DV + 1], Bw[kPtsQ][DW + 1];
         int64_t q[kPtsQ];
         bool ok[kPtsQ];
@@ -376,7 +385,150 @@ __global__ __launch_bounds__(kBlock) void k_tensor_points(const T *__restrict__ 
     }
 }
 
-// ------------------------------------------------------------------ MFMA grid
+// ------------------------------------------------------------------ MFMA points
+// Volumes of degrees up to 3 on the FP32 matrix cores.  A wavefront takes 64
+// points of one object.  Each lane forms the three bases of its own point and
+// shares them through LDS; the 64 points are then four tiles of 16, and per
+// tile and coordinate one 16x16x4 MFMA contracts w: rows m = 4 i + j of the net
+// (A: P[c][i][j][k], held for the whole object), columns the tile's points (B:
+// Bw_k).  Lane (g, n) = (l / 16, l mod 16) then holds i = g, j = 0..3 of point
+// n, contracts v on the vector ALU, and the four lanes of a point are added,
+// times Bu_i, while the four tiles are put side by side: two exchanges between
+// half-wavefronts or rows per coordinate leave lane l with point l, so that
+// every coordinate is stored as 64 consecutive floats.
+// About 125 vector instructions and 12 MFMAs (32 cycles of the matrix core each)
+// per 64 points, where the separable contraction on the vector ALU issues 355;
+// the two hardly overlap, and both draw the clock down when launches follow one
+// another.  65536 tricubics x 256: 148-157 -> 111-134 us (one card, another);
+// biquadratic in u and v, cubic in w: 64 -> 60; with w linear the vector ALU is
+// faster (54 against 66), so w has to be of degree 2 at least.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Bernstein basis of degree up to 3 with the rounding of 1 - t carried along:
+// ds is what 1 - t lost (exactly), and s^2 takes it up.  The basis is most of a
+// point's error: 0.97e-7 against 1.25e-7 of the points' norm (64-bit reference)
+// for tricubic points contracted either way.
+template <int D>
+__device__ __forceinline__ void bernstein_basis_comp(float t, float (&B)[D + 1]) {
+    const float s = 1.0f - t, d = (1.0f - s) - t, ds = d == d ? d : 0.0f;  // (t infinite: nothing lost)
+    if constexpr (D == 1) {
+        B[0] = s;
+        B[1] = t;
+    } else {
+        const float s2 = __builtin_fmaf(s, s, (s + s) * ds), t2 = t * t;
+        if constexpr (D == 2) {
+            const float a = 2.0f * t;
+            B[0] = s2;
+            B[1] = __builtin_fmaf(a, ds, a * s);
+            B[2] = t2;
+        } else {
+            B[0] = s2 * s;
+            B[1] = (3.0f * t) * s2;
+            B[2] = (3.0f * t2) * s;
+            B[3] = t2 * t;
+        }
+    }
+}
+
+// x, y: halves (rows) b of x exchanged with halves (rows) a of y.
+__device__ __forceinline__ void swap_halves(float &x, float &y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_rows(float &x, float &y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+}
+
+// Workgroup: four wavefronts of 64 points at a time, `per_wave` times; wavefront
+// w of object o begins at point w * per_wave * 64 of it.
+// (Four waves per SIMD asked for: with at most 256 registers per lane the compiler
+// lets the MFMAs write vector registers; otherwise 48 moves per 64 points fetch
+// their results from the accumulation registers, 148 against 134 us.)
+template <int DU, int DV, int DW, int DIM, typename T>
+__global__ __launch_bounds__(kBlock, 4) void k_tensor_points_mfma(const T *__restrict__ ctrl, const float *__restrict__ uvw,
+                                                               int64_t n_per, uint32_t n_obj, uint32_t waves_per_obj,
+                                                               int per_wave, float *__restrict__ out, int64_t plane,
+                                                               int64_t o0) {
+    constexpr int NCP = (DU + 1) * (DV + 1) * (DW + 1);
+    __shared__ __align__(16) float tab[kBlock / 64][3][64][4];
+    const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t w = blockIdx.x * (kBlock / 64) + wid;
+    const uint32_t o = w / waves_per_obj;
+    if (o >= n_obj) return;
+    const int64_t j_begin = static_cast<int64_t>(w - o * waves_per_obj) * per_wave * 64;
+    const int64_t j_end = min(n_per, j_begin + static_cast<int64_t>(per_wave) * 64);
+    if (j_begin >= j_end) return;
+    const T *__restrict__ P = ctrl + static_cast<size_t>(o) * DIM * NCP;
+    float A[DIM];  // row m = n: i = n / 4, j = n mod 4; k = g
+    {
+        const int i = n >> 2, j = n & 3;
+        const bool in = i <= DU && j <= DV && g <= DW;
+        const int at = in ? (i * (DV + 1) + j) * (DW + 1) + g : 0;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) A[c] = in ? to_f32<T>(P[c * NCP + at]) : 0.0f;
+    }
+    float (*__restrict__ tu)[4] = tab[wid][0], (*__restrict__ tv)[4] = tab[wid][1], (*__restrict__ tw)[4] = tab[wid][2];
+    const int64_t q0 = (o0 + o) * n_per + j_begin;
+    const int n_here = static_cast<int>(j_end - j_begin);
+    // parameters of point p of the wavefront's (of its last beyond), and its
+    // results, from wave-uniform bases
+    const float *__restrict__ up = uvw + q0 * 3;
+    float *__restrict__ ob = out + q0;
+    typedef float f32x3 __attribute__((ext_vector_type(3), aligned(4)));
+    auto params = [&](int p) {
+        return *reinterpret_cast<const f32x3 *>(reinterpret_cast<const char *>(up) +
+                                                static_cast<size_t>(12u * static_cast<uint32_t>(min(p, n_here - 1))));
+    };
+    f32x3 x = params(lane);
+    for (int p0 = 0; p0 < n_here; p0 += 64) {
+        float Bu[DU + 1], Bv[DV + 1], Bw[DW + 1];
+        bernstein_basis_comp<DU>(x[0], Bu);
+        bernstein_basis_comp<DV>(x[1], Bv);
+        bernstein_basis_comp<DW>(x[2], Bw);
+        if (p0 + 64 < n_here) x = params(p0 + 64 + lane);  // the next ones, on their way meanwhile
+        auto at = [](const auto &B, int i, int d) { return i <= d ? B[i] : 0.0f; };
+        // (the wavefront's own part of LDS: its instructions are in order, no barrier)
+        *reinterpret_cast<f32x4 *>(tu[lane]) = f32x4{Bu[0], at(Bu, 2, DU), Bu[1], at(Bu, 3, DU)};
+        *reinterpret_cast<f32x4 *>(tv[lane]) = f32x4{Bv[0], Bv[1], at(Bv, 2, DV), at(Bv, 3, DV)};
+        *reinterpret_cast<f32x4 *>(tw[lane]) = f32x4{Bw[0], Bw[1], at(Bw, 2, DW), at(Bw, 3, DW)};
+        __builtin_amdgcn_wave_barrier();
+        float R[4][DIM];  // tile, coordinate: contracted over w and v
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float b = tw[16 * t + n][g];
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(tv[16 * t + n]);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                const f32x4 q = __builtin_amdgcn_mfma_f32_16x16x4f32(A[c], b, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                float r = v[0] * q[0];
+#pragma unroll
+                for (int j = 1; j <= DV; ++j) r = __builtin_fmaf(v[j], q[j], r);
+                // (rows past the net are zero, but not times an infinite basis)
+                R[t][c] = DU == 3 || g <= DU ? r : 0.0f;
+            }
+        }
+        // Bu_i and Bu_(i+2), i = g mod 2, of this lane's tile of the pairs (0, 2) and (1, 3)
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        const int row = 16 * (g & 2) + n, pos = 2 * (g & 1);
+        const f32x2 u02 = *reinterpret_cast<const f32x2 *>(&tu[row][pos]);
+        const f32x2 u13 = *reinterpret_cast<const f32x2 *>(&tu[row + 16][pos]);
+        __builtin_amdgcn_wave_barrier();
+        const bool ok = p0 + lane < n_here;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            swap_halves(R[0][c], R[2][c]);
+            swap_halves(R[1][c], R[3][c]);
+            float a = __builtin_fmaf(u02[1], R[2][c], u02[0] * R[0][c]);
+            float b = __builtin_fmaf(u13[1], R[3][c], u13[0] * R[1][c]);
+            swap_rows(a, b);
+            if (ok) st_stream(at_lane(ob + c * plane, p0 + lane), a + b);
+        }
+    }
+}
 
 // ------------------------------------------------------------------ dispatch (over degrees and dim)
 template <typename T, int BASIS, int DU, int DV, int DIM>
@@ -432,16 +584,49 @@ int launch_grid(int du, int dv, int dim, const void *ctrl, int nu, int nv, float
     }
 }
 
+// Which kernel (see k_tensor_points_mfma).
+template <int BASIS, int DU, int DV, int DW>
+constexpr bool kPointsMfma = BASIS == kBasisBernstein && DW >= 2 && DU <= 3 && DV <= 3 && DW <= 3 &&
+                             (DU + 1) * (DV + 1) * (DW + 1) >= 27;
+
+template <typename T, int BASIS, int DU, int DV, int DW, int DIM>
+void launch_pts4(const void *ctrl, const float *uvw, int64_t n_per, float *out, int64_t plane, int64_t o0,
+                 uint32_t n_obj, hipStream_t s) {
+    constexpr bool MFMA = kPointsMfma<BASIS, DU, DV, DW>;
+    // pieces of an object's queries, 64 times the queries per lane; up to 4 x 64
+    // queries per wavefront while that leaves 16 wavefronts per CU (626 tricubics
+    // x 604: 12.5 us with a wavefront per object, 6.2 so; 200 bicubics x 600: 7.8
+    // and 4.6)
+    const int q = MFMA ? 1 : kPtsQ;
+    const int64_t pieces = (n_per + 64 * q - 1) / (64 * q);
+    const int64_t most = MFMA ? 4 : 1;
+    const int64_t per = std::max<int64_t>({1, std::min({most, pieces, n_obj * pieces / 4096}), (pieces + (1 << 20)) >> 21});
+    const uint32_t wpo = static_cast<uint32_t>((pieces + per - 1) / per);
+    // at most 2^25 wavefronts per launch
+    const int64_t step = std::max<int64_t>(1, (int64_t(1) << 25) / wpo);
+    for (int64_t i = 0; i < n_obj; i += step) {
+        const uint32_t no = static_cast<uint32_t>(std::min<int64_t>(step, n_obj - i));
+        const uint64_t waves = static_cast<uint64_t>(no) * wpo;
+        const dim3 blocks(static_cast<uint32_t>((waves + kBlock / 64 - 1) / (kBlock / 64)));
+        const T *p = static_cast<const T *>(ctrl) + i * DIM * (DU + 1) * (DV + 1) * (DW + 1);
+        const int pw = static_cast<int>(per);
+        if constexpr (MFMA)
+            hipLaunchKernelGGL((k_tensor_points_mfma<DU, DV, DW, DIM, T>), blocks, dim3(kBlock), 0, s, p, uvw, n_per, no,
+                               wpo, pw, out, plane, o0 + i);
+        else
+            hipLaunchKernelGGL((k_tensor_points<DU, DV, DW, DIM, T, BASIS>), blocks, dim3(kBlock), 0, s, p, uvw, n_per,
+                               no, wpo, pw, out, plane, o0 + i);
+    }
+}
+
 template <typename T, int BASIS, int DU, int DV, int DW>
 int launch_pts3(int dim, const void *ctrl, const float *uvw, int64_t n_per, float *out, int64_t plane, int64_t o0,
                 uint32_t n_obj, hipStream_t s) {
-    const T *p = static_cast<const T *>(ctrl);
-    const uint32_t blocks = (n_obj + kBlock / 64 - 1) / (kBlock / 64);
     switch (dim) {
-        case 1: hipLaunchKernelGGL((k_tensor_points<DU, DV, DW, 1, T, BASIS>), dim3(blocks), dim3(kBlock), 0, s, p, uvw, n_per, n_obj, out, plane, o0); break;
-        case 2: hipLaunchKernelGGL((k_tensor_points<DU, DV, DW, 2, T, BASIS>), dim3(blocks), dim3(kBlock), 0, s, p, uvw, n_per, n_obj, out, plane, o0); break;
-        case 3: hipLaunchKernelGGL((k_tensor_points<DU, DV, DW, 3, T, BASIS>), dim3(blocks), dim3(kBlock), 0, s, p, uvw, n_per, n_obj, out, plane, o0); break;
-        default: hipLaunchKernelGGL((k_tensor_points<DU, DV, DW, 4, T, BASIS>), dim3(blocks), dim3(kBlock), 0, s, p, uvw, n_per, n_obj, out, plane, o0); break;
+        case 1: launch_pts4<T, BASIS, DU, DV, DW, 1>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
+        case 2: launch_pts4<T, BASIS, DU, DV, DW, 2>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
+        case 3: launch_pts4<T, BASIS, DU, DV, DW, 3>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
+        default: launch_pts4<T, BASIS, DU, DV, DW, 4>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
     }
     return BZ_OK;
 }
