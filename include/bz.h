@@ -398,9 +398,10 @@ int bz_batch_eval_uv(bz_plan plan, const float *t, const float *v, float *out, b
  * schedules (atomic tile counter, static round robin) x 4 grid sizes (4, 8,
  * 12, 16 workgroups per CU) and keeps the fastest in the plan.
  * (The timing launches of a plan with patches read the patches' v from t.)  Without
- * autotuning a plan launches 8 workgroups per CU, 4 sub-tiles per tile, the
- * static schedule, windows of 2^17 objects and four parameters per lane when
- * n_t is a multiple of 4.  Synchronises the stream.  best6 (nullable, host, 6
+ * autotuning a plan launches 8 workgroups per CU with the static schedule and
+ * windows of 2^17 objects; 4 sub-tiles per tile and, when n_t is a multiple of
+ * 4, four parameters per lane, or less of both where a batch is too small to
+ * give every CU a tile.  No launch has more workgroups than tiles.  Synchronises the stream.  best6 (nullable, host, 6
  * values): workgroups, sub-tiles per tile, microseconds per launch, schedule
  * (1 dynamic, 0 static), queries per lane, window (0: class-major).
  */

@@ -183,6 +183,27 @@ bool build_nurbs_tables(const std::vector<int32_t> &seg_first, const std::vector
 // Objects per window of the default tile order (see build_tiles).
 constexpr uint32_t kDefaultWindow = 131072;
 
+// Sub-tiles per tile and queries per lane of a plan that is not tuned: the
+// largest tiles that still give every CU one, for a tile's sub-tiles and a
+// lane's queries run one after another (4 sub-tiles x 4 queries, 4 x 1, 2 x 1 or
+// 1 x 1).  32,000 objects x 16 (FP32): 12.5 us with 168 tiles of 4 x 4, 8.3 with
+// 513 of 4 x 1; 87,000: 16.7 with 438 of 4 x 4, 17.8 with 1455 of 4 x 1; 6,500 x
+// 8: 7.0 with 32 of 4 x 4, 5.6 with 219 of 1 x 1.
+void default_tiles(const std::vector<ClassInfo> &cls, int64_t n_t, uint32_t cus, uint32_t *qpt, uint32_t *vq) {
+    const uint32_t choices[][2] = {{4, 4}, {4, 1}, {2, 1}, {1, 1}};
+    for (const auto &c : choices) {
+        if (c[1] == 4 && n_t % 4 != 0) continue;
+        *qpt = c[0];
+        *vq = c[1];
+        int64_t tiles = 0;
+        for (const ClassInfo &ci : cls) {
+            const int64_t span = static_cast<int64_t>(kBlock) * c[0] * (ci.kind == 2 || ci.kind == 3 ? 1 : c[1]);
+            tiles += (ci.count * n_t + span - 1) / span;
+        }
+        if (tiles >= cus) return;
+    }
+}
+
 int class_cost(int kind, int degree, int method, int dim) {
     const int ch = dim + (kind != 0 ? 1 : 0);
     if (kind == 2) return 60 + 4 * ch;
@@ -272,6 +293,7 @@ int launch_batch(const bz_plan_s *p, const float *t, const float *v, float *out,
     a.dim = p->dim;
     a.counters = p->counters;
     const bool dc = p->method == BZ_DECASTELJAU;
+    workgroups = std::min(workgroups, std::max(1u, p->n_tiles));  // no more than there are tiles
     if (p->dtype == BZ_F32)
         return dc ? launch_batch_kernel<FORM_DC, float>(workgroups, a, s)
                   : launch_batch_kernel<FORM_BERN, float>(workgroups, a, s);
@@ -558,7 +580,18 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             if (!rc) rc = dev_upload(&p->nhead, nh, s);
             if (!rc && !nt.empty()) rc = dev_upload(&p->ntab, nt, s);
         }
-        if (!rc) rc = build_tiles(p, 4, n_t % 4 == 0 ? 4 : 1, kDefaultWindow, s);
+        if (!rc) {
+            int dev = 0, cus = 0;
+            hipError_t e = hipGetDevice(&dev);
+            if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+            if (e != hipSuccess) rc = hip_fail(e, "device query");
+            p->cus = static_cast<uint32_t>(std::max(1, cus));
+        }
+        if (!rc) {
+            uint32_t qpt = 1, vq = 1;
+            default_tiles(cls, n_t, p->cus, &qpt, &vq);
+            rc = build_tiles(p, qpt, vq, kDefaultWindow, s);
+        }
         if (!rc) rc = dmalloc(&p->ctrl_s, ctrl_elems * es);
         if (!rc) rc = dmalloc(&p->w_s, w_elems * es);
         if (!rc) rc = dmalloc(reinterpret_cast<void **>(&p->seg), std::max<int64_t>(p->n_segs, 1) * 4 * (dim + 1) * sizeof(float));
@@ -615,15 +648,8 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             }
         }
         if (!rc) {
-            // default launch: the configuration the autotuner picks on MI355X for
-            // mixed batches (static schedule, four sub-tiles per tile, four
-            // parameters per lane where n_t allows, windows of 2^17 objects,
-            // eight workgroups per CU)
-            int dev = 0, cus = 0;
-            hipError_t e = hipGetDevice(&dev);
-            if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-            if (e != hipSuccess) rc = hip_fail(e, "device query");
-            p->cus = static_cast<uint32_t>(std::max(1, cus));
+            // default launch: static schedule, eight workgroups per CU (or one per
+            // tile, if there are fewer), as the autotuner picks for mixed batches
             p->workgroups = 8 * p->cus;
             p->dynamic = 0;
         }
