@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kBlock) void k_nurbs_extract(int n_nurbs, const int
 // bucket m then lies in segments tab[m].s .. tab[m+1].s, because the bucket
 // function is monotone.  Returns false if an entry is out of range (which the
 // construction excludes; checked before anything reaches the device).
-// with_table false: the headers alone (16-bit plans search the breakpoints).
+// with_table false: the headers alone.
 bool build_nurbs_tables(const std::vector<int32_t> &seg_first, const std::vector<float> &brk,
                         std::vector<NurbsHead> &head, std::vector<NurbsTab> &tab, bool with_table) {
     const size_t n = seg_first.size() - 1;
@@ -574,8 +574,8 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
         if (!rc) {
             std::vector<NurbsHead> nh;
             std::vector<NurbsTab> nt;
-            // the span table serves FP32 plans only (see NurbsHead)
-            if (!build_nurbs_tables(seg_first, brk, nh, nt, dtype == BZ_F32))
+            // (16-bit plans of many segments search instead, see NurbsHead)
+            if (!build_nurbs_tables(seg_first, brk, nh, nt, dtype == BZ_F32 || seg_first.back() <= kTableSegs))
                 rc = fail(BZ_ERR_INTERNAL, "%s: NURBS span table", fn);
             if (!rc) rc = dev_upload(&p->nhead, nh, s);
             if (!rc && !nt.empty()) rc = dev_upload(&p->ntab, nt, s);

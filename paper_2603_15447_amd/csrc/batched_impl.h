@@ -29,22 +29,28 @@ struct Tile {
 };
 
 // Span lookup of a NURBS query, two ways (the persistent kernel takes the
-// faster for its storage type, measured on a mixed batch in steady state):
-// - bucket table (FP32 storage): the parameter range [lo, hi] of NURBS r is
-//   cut into M = 2*nseg equal buckets; a parameter of bucket m lies in one of
-//   the segments tab[m].s .. tab[m+1].s (indices relative to the NURBS), and
-//   when those are two segments, tab[m].split (the breakpoint between them)
-//   decides.  More than two candidates (two or more breakpoints in one
-//   bucket) fall back to a binary search over the breakpoints of that range.
-// - binary search over the NURBS's nseg+1 breakpoints (16-bit storage): a line
-//   or two that the 16 queries of a NURBS share, where the table costs one
+// faster for its storage type and size, measured in steady state):
+// - bucket table (FP32 storage, and 16-bit plans of up to kTableSegs segments):
+//   the parameter range [lo, hi] of NURBS r is cut into M = 2*nseg equal
+//   buckets; a parameter of bucket m lies in one of the segments tab[m].s ..
+//   tab[m+1].s (indices relative to the NURBS), and when those are two segments,
+//   tab[m].split (the breakpoint between them) decides.  More than two candidates
+//   (two or more breakpoints in one bucket) fall back to a binary search over the
+//   breakpoints of that range.
+// - binary search over the NURBS's nseg+1 breakpoints (larger 16-bit plans): a
+//   line or two that the 16 queries of a NURBS share, where the table costs one
 //   more random line per query.  With FP32 control rows streaming past, the
 //   search's dependent probes miss the cache and the table is faster; with
-//   16-bit rows they hit, and the search is.
+//   16-bit rows they hit, and the search is.  In a small plan, where everything
+//   hits, only the length of the chain counts, and the table's is shorter: 3300
+//   objects x 10 with 5,706 segments 7.2 us by search, 5.8 by table; 17,000 x 16
+//   with 28,500: 7.4 and 6.9; from 55,000 segments on the same.
+constexpr int64_t kTableSegs = 32768;
+
 struct NurbsHead {
     int32_t s0;    // first segment of the NURBS in the plan's segment array
     int32_t nseg;  // segments (non-empty knot spans)
-    int32_t tab0;  // first of its 2*nseg+1 table entries
+    int32_t tab0;  // first of its 2*nseg+1 table entries (if the plan has a table)
     int32_t brk0;  // first of its nseg+1 breakpoints (s0 + rank)
     float lo, hi;  // parameter range
     float inv_h;   // M / (hi - lo); 0 when that is not finite (one bucket)
@@ -83,7 +89,7 @@ struct BatchArgs {
     uint32_t n_tiles;          // tiles of the persistent launch
     uint32_t n_signed;         // tiles of signed-weight rationals, after those (a launch of their own)
     const NurbsHead *nhead;    // [n_nurbs], NURBS ranked in sorted order
-    const NurbsTab *ntab;      // span lookup tables, 2*nseg+1 entries per NURBS (FP32 storage only)
+    const NurbsTab *ntab;      // span lookup tables, 2*nseg+1 entries per NURBS; null: search
     const float *brk;          // breakpoints, nseg+1 per NURBS, from NurbsHead::brk0
     const float *seg;          // [n_segs][4][dim+1] homogeneous
     const float *t;
@@ -701,7 +707,8 @@ __device__ __forceinline__ void run_tile(const BatchArgs &a, unsigned int tile, 
     if (tl.ci.kind == 0) dispatch_degree<false, F, T, VQ>(a, tl, out);
     else if (tl.ci.kind == 1) dispatch_degree<true, F, T, VQ>(a, tl, out);
     else if (tl.ci.kind == 4) dispatch_patch<F, T, VQ>(a, tl, out);
-    else run_nurbs_tile_dim<!std::is_same<T, float>::value>(a, tl, out);
+    else if (std::is_same<T, float>::value || a.ntab) run_nurbs_tile_dim<false>(a, tl, out);
+    else run_nurbs_tile_dim<true>(a, tl, out);
 }
 
 // Dynamic schedule: workgroups pull tiles from an atomic counter (the next
