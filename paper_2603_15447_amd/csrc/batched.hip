@@ -180,28 +180,41 @@ bool build_nurbs_tables(const std::vector<int32_t> &seg_first, const std::vector
     return true;
 }
 
-// Objects per window of the default tile order (see build_tiles).
-constexpr uint32_t kDefaultWindow = 131072;
+// Tile layout of a plan that is not tuned: sub-tiles per tile, queries per lane,
+// objects per window of the tile order (see build_tiles).
+struct Layout {
+    uint32_t qpt, vq, window;
+};
 
-// Sub-tiles per tile and queries per lane of a plan that is not tuned: the
-// largest tiles that still give every CU one, for a tile's sub-tiles and a
-// lane's queries run one after another (4 sub-tiles x 4 queries, 4 x 1, 2 x 1 or
-// 1 x 1).  32,000 objects x 16 (FP32): 12.5 us with 168 tiles of 4 x 4, 8.3 with
+// Of the layouts for the row length, the first that gives every CU a tile, for
+// a tile's sub-tiles and a lane's queries run one after another: 32,000 objects
+// x 16 (FP32) take 12.5 us with 168 tiles of 4 sub-tiles x 4 queries, 8.3 with
 // 513 of 4 x 1; 87,000: 16.7 with 438 of 4 x 4, 17.8 with 1455 of 4 x 1; 6,500 x
 // 8: 7.0 with 32 of 4 x 4, 5.6 with 219 of 1 x 1.
-void default_tiles(const std::vector<ClassInfo> &cls, int64_t n_t, uint32_t cus, uint32_t *qpt, uint32_t *vq) {
-    const uint32_t choices[][2] = {{4, 4}, {4, 1}, {2, 1}, {1, 1}};
-    for (const auto &c : choices) {
-        if (c[1] == 4 && n_t % 4 != 0) continue;
-        *qpt = c[0];
-        *vq = c[1];
+// Rows of n_t parameters or points that are whole 64-byte pieces are best read
+// and written four at a time, in large windows (2^20 curves x 16: 138 us).
+// Other rows share their pieces with their neighbours', which belong to other
+// classes: smaller windows bring those together in the caches (400,000 objects
+// x 10: 74 us with windows of 2^17, 66 with 2^14; 300,000 x 25: 94 and 83), one
+// query per lane spreads short rows less (900,000 x 8 in windows of 2^15: 156 us
+// with 4 x 4, 138 with 4 x 1; 400,000 x 12: 82 and 68), and of longer ones two
+// sub-tiles do better than four (300,000 x 24: 64 us, 72 with four or with one
+// query per lane).
+Layout default_layout(const std::vector<ClassInfo> &cls, int64_t n_t, uint32_t cus) {
+    std::vector<Layout> choices;
+    if (n_t % 16 == 0) choices = {{4, 4, 1u << 17}, {4, 1, 1u << 17}, {2, 1, 1u << 17}, {1, 1, 1u << 17}};
+    else if (n_t > 16 && n_t % 4 == 0) choices = {{2, 4, 1u << 15}, {4, 1, 1u << 15}, {2, 1, 1u << 15}, {1, 1, 1u << 15}};
+    else if (n_t % 4 == 0) choices = {{4, 1, 1u << 15}, {2, 1, 1u << 15}, {1, 1, 1u << 15}};
+    else choices = {{4, 1, 1u << 14}, {2, 1, 1u << 14}, {1, 1, 1u << 14}};
+    for (const Layout &l : choices) {
         int64_t tiles = 0;
         for (const ClassInfo &ci : cls) {
-            const int64_t span = static_cast<int64_t>(kBlock) * c[0] * (ci.kind == 2 || ci.kind == 3 ? 1 : c[1]);
+            const int64_t span = static_cast<int64_t>(kBlock) * l.qpt * (ci.kind == 2 || ci.kind == 3 ? 1 : l.vq);
             tiles += (ci.count * n_t + span - 1) / span;
         }
-        if (tiles >= cus) return;
+        if (tiles >= cus) return l;
     }
+    return choices.back();
 }
 
 int class_cost(int kind, int degree, int method, int dim) {
@@ -588,9 +601,8 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             p->cus = static_cast<uint32_t>(std::max(1, cus));
         }
         if (!rc) {
-            uint32_t qpt = 1, vq = 1;
-            default_tiles(cls, n_t, p->cus, &qpt, &vq);
-            rc = build_tiles(p, qpt, vq, kDefaultWindow, s);
+            const Layout l = default_layout(cls, n_t, p->cus);
+            rc = build_tiles(p, l.qpt, l.vq, l.window, s);
         }
         if (!rc) rc = dmalloc(&p->ctrl_s, ctrl_elems * es);
         if (!rc) rc = dmalloc(&p->w_s, w_elems * es);
@@ -648,9 +660,11 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             }
         }
         if (!rc) {
-            // default launch: static schedule, eight workgroups per CU (or one per
-            // tile, if there are fewer), as the autotuner picks for mixed batches
-            p->workgroups = 8 * p->cus;
+            // default launch: a workgroup per tile (up to 64 per CU), handed out by
+            // the hardware as CUs come free: 2^20 curves and 2^16 NURBS x 16, 145 us
+            // with 8 workgroups per CU going round the tiles, 138 so (152 and 142
+            // with FP16 storage; 500,000 curves: 77 and 76)
+            p->workgroups = 64 * p->cus;
             p->dynamic = 0;
         }
         if (!rc) rc = hipStreamSynchronize(s) == hipSuccess ? BZ_OK : fail(BZ_ERR_HIP, "%s: sync", fn);
@@ -698,17 +712,14 @@ int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream s
         int best_dyn = plan->dynamic;
         const uint32_t qpts[] = {1, 2, 4};
         const uint32_t vqs[] = {1, 4};
-        const uint32_t wg_per_cu[] = {4, 8, 12, 16};
+        const uint32_t wg_per_cu[] = {8, 12, 16, 64};
         const uint32_t windows[] = {0, 32768, 131072, 262144};
-        struct Layout {
-            uint32_t win, vq, q;
-        };
         std::vector<Layout> layouts;
         for (uint32_t win : windows) {
             if (win != 0 && win >= plan->n_obj) continue;  // one window is the class-major order
             for (uint32_t vq : vqs) {
                 if (vq == 4 && plan->n_t % 4 != 0) continue;  // four queries of one object per lane
-                for (uint32_t q : qpts) layouts.push_back(Layout{win, vq, q});
+                for (uint32_t q : qpts) layouts.push_back(Layout{q, vq, win});
             }
         }
         // best of three rounds of 5 launches: one round is noisy enough to rank
@@ -732,7 +743,7 @@ int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream s
         };
         int rc = BZ_OK;
         for (const Layout &L : layouts) {
-            rc = build_tiles(plan, L.q, L.vq, L.win, s);
+            rc = build_tiles(plan, L.qpt, L.vq, L.window, s);
             if (rc) break;
             for (int dyn = 1; dyn >= 0 && !rc; --dyn)
                 for (uint32_t f : wg_per_cu) {
@@ -742,10 +753,10 @@ int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream s
                     if (ms < best) {
                         best = ms;
                         best_wg = f * cus;
-                        best_q = L.q;
+                        best_q = L.qpt;
                         best_dyn = dyn;
                         best_vq = L.vq;
-                        best_win = L.win;
+                        best_win = L.window;
                     }
                 }
             if (rc) break;
