@@ -344,8 +344,8 @@ int bz_eval_tensor_seiler(const float *sc, int64_t n_obj, int du, int dv, int dw
 
 /*
  * Mixed batches in one persistent launch: integral and rational Bezier
- * curves of degree 1..15, cubic NURBS (Sec. 2.2: B-splines are converted to
- * rational Bezier segments by knot insertion) and tensor-product surface
+ * curves of degree 1..15, cubic NURBS (Sec. 2.2: rational splines; evaluated
+ * by Cox and de Boor's recursion) and tensor-product surface
  * patches (Sec. 2.2).  All descriptor arrays are device pointers:
  *   kind_degree[n_obj]   kind << 8 | degree; kind 0 Bezier, 1 rational,
  *                        2 NURBS (degree must be 3), 3 surface patch with
@@ -361,11 +361,10 @@ int bz_eval_tensor_seiler(const float *sc, int64_t n_obj, int du, int dv, int dw
  *   n_t                  parameters per object
  * The plan reads the descriptor (synchronously), sorts objects into
  * uniform classes (kind, degree), copies the control points and weights of
- * the Bezier objects into class-sorted contiguous order, extracts the
- * rational Bezier segments of every NURBS on the GPU and keeps all of that in
- * its own device memory: none of the descriptor arrays, ctrl or w is used
- * after bz_batch_plan_create returns (changed control points need a new
- * plan).  Parameters t[n_obj][n_t] (NURBS parameters are clamped to the knot
+ * the objects into class-sorted contiguous order (each NURBS's beside its knots
+ * and a knot span table) and keeps all of that in its own device memory: none
+ * of the descriptor arrays, ctrl or w is used after bz_batch_plan_create
+ * returns (changed control points need a new plan).  Parameters t[n_obj][n_t] (NURBS parameters are clamped to the knot
  * range; a patch's u) and out[dim][n_obj*n_t] are passed per evaluation (out
  * must not overlap t); a plan with patches is evaluated by bz_batch_eval_uv,
  * whose v[n_obj][n_t] holds the patches' second parameters (only the rows of
@@ -417,7 +416,8 @@ int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream s
  */
 int bz_batch_plan_configure(bz_plan plan, int64_t workgroups, int sub_tiles, int schedule, int queries_per_lane,
                             int64_t window, bz_stream stream);
-/* Plan statistics: n_classes, n_tiles, n_segments (NURBS), workgroups. */
+/* Plan statistics: n_classes, n_tiles, n_segments (non-empty knot spans of the
+ * NURBS), workgroups. */
 int bz_batch_plan_info(bz_plan plan, int64_t *info4);
 int bz_plan_destroy(bz_plan plan);
 

@@ -3,10 +3,9 @@
 //
 // Plan (host, once): objects are sorted into uniform classes (kind, degree)
 // so that every 256-query tile, and hence every wavefront, runs one code path;
-// NURBS are cut into rational Bezier segments by knot insertion on the GPU
-// (Sec. 2.2: B-splines become piecewise Bezier curves via Boehm's algorithm)
-// with the breakpoints kept for a per-query span search; tiles are ordered by
-// estimated cost, heaviest first.
+// NURBS control points are gathered with their weights, beside their knots and
+// a table for the per-query span lookup; tiles are ordered by estimated cost,
+// heaviest first.
 // Evaluation (batched_impl.h): a grid of (CUs x occupancy) workgroups takes
 // tiles round-robin or from an atomic counter; the last workgroup to finish
 // resets the counters, so consecutive launches (and graph replays) need no
@@ -68,115 +67,59 @@ __global__ __launch_bounds__(kBlock) void k_weight_flags(int64_t n_obj, const ui
     flags[o] = f;
 }
 
-// Bezier extraction of one clamped cubic NURBS by knot insertion: every
-// interior knot is raised to multiplicity p, leaving one rational Bezier
-// segment (4 homogeneous points) per non-empty knot span.  Works left to
-// right on a window of p+1 points, so only O(p) state is kept.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_nurbs_extract(int n_nurbs, const int64_t *__restrict__ nurbs_obj,
-                                                          const int64_t *__restrict__ cp_offset,
-                                                          const int64_t *__restrict__ knot_offset,
-                                                          const T *__restrict__ ctrl, const T *__restrict__ w,
-                                                          const float *__restrict__ knots,
-                                                          const int32_t *__restrict__ seg_first, int dim,
-                                                          float *__restrict__ seg) {
-    const int r = blockIdx.x * kBlock + threadIdx.x;
+// Plan-time copy of the NURBS control points, point by point with the weight
+// last (storage bits unchanged).  One wavefront per NURBS.
+template <typename U>
+__global__ __launch_bounds__(kBlock) void k_gather_nurbs(int n_nurbs, const int64_t *__restrict__ nurbs_obj,
+                                                         const int64_t *__restrict__ cp_offset,
+                                                         const NurbsHead *__restrict__ head, int dim,
+                                                         const U *__restrict__ ctrl, const U *__restrict__ w,
+                                                         U *__restrict__ pts) {
+    const int r = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
     if (r >= n_nurbs) return;
-    constexpr int p = kNurbsP;
-    const int64_t o = nurbs_obj[r];
-    const int64_t cp = cp_offset[o];
-    const int ncp = static_cast<int>(cp_offset[o + 1] - cp);
-    const float *U = knots + knot_offset[o];
-    const int m = ncp + p;  // index of the last knot
-    const T *P = ctrl + cp * dim;
-    const T *Wt = w + cp;
+    const int64_t cp = cp_offset[nurbs_obj[r]];
+    const int64_t ncp = cp_offset[nurbs_obj[r] + 1] - cp;
     const int H = dim + 1;
-    auto pw = [&](int i, int k) -> double {  // homogeneous control point i, coordinate k
-        const double wi = static_cast<double>(to_f32<T>(Wt[i]));
-        return k == dim ? wi : wi * static_cast<double>(to_f32<T>(P[static_cast<int64_t>(k) * ncp + i]));
-    };
-    double Q[p + 1][kMaxDim + 1], Nx[p + 1][kMaxDim + 1];
-    for (int i = 0; i <= p; ++i)
-        for (int k = 0; k < H; ++k) Q[i][k] = pw(i, k);
-    float *out = seg + static_cast<size_t>(seg_first[r]) * 4 * H;
-    const int nseg = seg_first[r + 1] - seg_first[r];
-    int a = p, b = p + 1, ns = 0;
-    while (b < m && ns < nseg) {
-        const int i0 = b;
-        while (b < m && U[b + 1] == U[b]) ++b;
-        const int mult = b - i0 + 1;
-        int rr = 0;
-        if (mult < p) {
-            const double numer = static_cast<double>(U[b]) - U[a];
-            double alpha[p];
-            for (int j = p; j > mult; --j) alpha[j - mult - 1] = numer / (static_cast<double>(U[a + j]) - U[a]);
-            rr = p - mult;
-            for (int j = 1; j <= rr; ++j) {
-                const int save = rr - j, s = mult + j;
-                for (int k = p; k >= s; --k) {
-                    const double al = alpha[k - s];
-                    for (int c = 0; c < H; ++c) Q[k][c] = al * Q[k][c] + (1.0 - al) * Q[k - 1][c];
-                }
-                if (b < m)
-                    for (int c = 0; c < H; ++c) Nx[save][c] = Q[p][c];
-            }
-        }
-        for (int i = 0; i <= p; ++i)
-            for (int c = 0; c < H; ++c) out[(static_cast<size_t>(ns) * 4 + i) * H + c] = static_cast<float>(Q[i][c]);
-        ++ns;
-        if (b < m) {
-            for (int i = (mult < p ? p - mult : 0); i <= p; ++i)
-                for (int c = 0; c < H; ++c) Nx[i][c] = pw(b - p + i, c);
-            for (int i = 0; i <= p; ++i)
-                for (int c = 0; c < H; ++c) Q[i][c] = Nx[i][c];
-            a = b;
-            ++b;
-        }
+    const U *P = ctrl + cp * dim;
+    U *dst = pts + static_cast<int64_t>(head[r].cp0) * H;
+    for (int64_t e = threadIdx.x & 63; e < ncp * H; e += 64) {
+        const int64_t i = e / H, k = e - i * H;
+        dst[e] = k == dim ? w[cp + i] : P[k * ncp + i];
     }
 }
 
-// Span lookup tables of the NURBS (see NurbsHead): for bucket m, the first
-// segment whose end breakpoint lies in bucket m or later; a parameter of
-// bucket m then lies in segments tab[m].s .. tab[m+1].s, because the bucket
-// function is monotone.  Returns false if an entry is out of range (which the
-// construction excludes; checked before anything reaches the device).
-// with_table false: the headers alone.
-bool build_nurbs_tables(const std::vector<int32_t> &seg_first, const std::vector<float> &brk,
-                        std::vector<NurbsHead> &head, std::vector<NurbsTab> &tab, bool with_table) {
-    const size_t n = seg_first.size() - 1;
-    head.resize(n);
-    tab.clear();
-    tab.reserve(2 * static_cast<size_t>(seg_first.back()) + n);
-    std::vector<int> bk;
-    for (size_t r = 0; r < n; ++r) {
-        NurbsHead h{};
-        h.s0 = seg_first[r];
-        h.nseg = seg_first[r + 1] - seg_first[r];
-        h.brk0 = h.s0 + static_cast<int32_t>(r);
-        h.tab0 = static_cast<int32_t>(tab.size());
-        const float *b = brk.data() + h.brk0;
-        h.lo = b[0];
-        h.hi = b[h.nseg];
-        const int M = 2 * h.nseg;
-        h.inv_h = static_cast<float>(M) / (h.hi - h.lo);
-        if (!std::isfinite(h.inv_h)) h.inv_h = 0.0f;  // one bucket holds every segment
-        if (!with_table) {
-            head[r] = h;
-            continue;
-        }
-        bk.resize(h.nseg + 1);
-        for (int i = 0; i <= h.nseg; ++i) bk[i] = nurbs_bucket(b[i], h.lo, h.inv_h, M);
-        int i = 0;
-        for (int m = 0; m <= M; ++m) {
-            while (i < h.nseg - 1 && bk[i + 1] < m) ++i;
-            tab.push_back(NurbsTab{i, b[i + 1]});
-        }
-        for (int m = 0; m <= M; ++m) {
-            const int32_t v = tab[h.tab0 + m].s;
-            if (v < 0 || v >= h.nseg || (m > 0 && v < tab[h.tab0 + m - 1].s)) return false;
-        }
-        head[r] = h;
+// Header and span table of one NURBS (see NurbsHead): for bucket m, the first
+// span whose end lies in bucket m or later; a parameter of bucket m then lies in
+// spans tab[m] .. tab[m+1], because the bucket function is monotone.  u: its
+// ncp+4 knots; spans: the first knots of its non-empty spans.  Returns false if
+// an entry is out of range (which the construction excludes; checked before
+// anything reaches the device).
+bool add_nurbs(const float *u, int64_t ncp, const std::vector<int32_t> &spans, int64_t cp0,
+               std::vector<NurbsHead> &head, std::vector<uint16_t> &tab, std::vector<int> &bk) {
+    NurbsHead h{};
+    const int n = static_cast<int>(spans.size()), M = 2 * n;
+    h.cp0 = static_cast<int32_t>(cp0);
+    h.lo = u[kNurbsP];
+    h.hi = u[ncp];
+    h.inv_h = static_cast<float>(M) / (h.hi - h.lo);
+    if (!std::isfinite(h.inv_h)) h.inv_h = 0.0f;  // one bucket holds every span
+    if (ncp > 65535) {
+        h.tab0 = -1;
+        h.n_buckets = spans.back();
+        head.push_back(h);
+        return true;
     }
+    h.tab0 = static_cast<int32_t>(tab.size());
+    h.n_buckets = M;
+    bk.resize(n);
+    for (int i = 0; i < n; ++i) bk[i] = nurbs_bucket(u[spans[i] + 1], h.lo, h.inv_h, M);  // the span's end
+    int i = 0;
+    for (int m = 0; m <= M; ++m) {
+        while (i < n - 1 && bk[i] < m) ++i;
+        tab.push_back(static_cast<uint16_t>(spans[i]));
+        if (spans[i] < kNurbsP || spans[i] >= ncp) return false;
+    }
+    head.push_back(h);
     return true;
 }
 
@@ -242,10 +185,10 @@ struct bz_plan_s {
     void *ctrl_s = nullptr, *w_s = nullptr;
     int32_t *perm = nullptr;
     Tile *tiles = nullptr;
-    int32_t *seg_first = nullptr;
     NurbsHead *nhead = nullptr;
-    NurbsTab *ntab = nullptr;
-    float *brk = nullptr, *seg = nullptr;
+    uint16_t *ntab = nullptr;
+    float *nknots = nullptr;
+    void *npts = nullptr;
     unsigned int *counters = nullptr;
     std::vector<ClassInfo> classes;
     std::vector<int32_t> perm_h;  // host copy of perm (window boundaries of the tile order)
@@ -260,8 +203,7 @@ namespace {
 
 void plan_free(bz_plan_s *p) {
     if (!p) return;
-    void *bufs[] = {p->ctrl_s, p->w_s, p->perm, p->tiles, p->seg_first, p->nhead, p->ntab, p->brk, p->seg,
-                    p->counters};
+    void *bufs[] = {p->ctrl_s, p->w_s, p->perm, p->tiles, p->nhead, p->ntab, p->nknots, p->npts, p->counters};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     delete p;
@@ -295,8 +237,8 @@ int launch_batch(const bz_plan_s *p, const float *t, const float *v, float *out,
     a.n_signed = p->n_signed;
     a.nhead = p->nhead;
     a.ntab = p->ntab;
-    a.brk = p->brk;
-    a.seg = p->seg;
+    a.nknots = p->nknots;
+    a.npts = p->npts;
     a.t = t;
     a.v = v;
     a.out = out;
@@ -334,10 +276,11 @@ int build_tiles(bz_plan_s *p, uint32_t qpt, uint32_t vq, uint32_t window, hipStr
     });
     std::vector<Tile> tiles;
     auto emit = [&](int c, uint64_t a, uint64_t b) {  // queries [a, b) of class c
+        const uint32_t sub = cls[c].kind == 2 ? std::min(qpt, nurbs_sub_tiles(p->dtype == BZ_F32)) : qpt;
         const uint64_t span =
-            static_cast<uint64_t>(kBlock) * qpt * (cls[c].kind == 0 || cls[c].kind == 1 || cls[c].kind == 4 ? vq : 1);
+            static_cast<uint64_t>(kBlock) * sub * (cls[c].kind == 0 || cls[c].kind == 1 || cls[c].kind == 4 ? vq : 1);
         for (uint64_t q0 = a; q0 < b; q0 += span)
-            tiles.push_back(Tile{cls[c], static_cast<uint32_t>(q0), static_cast<uint32_t>(b), qpt, 0});
+            tiles.push_back(Tile{cls[c], static_cast<uint32_t>(q0), static_cast<uint32_t>(b), sub, 0});
     };
     const uint64_t nt = static_cast<uint64_t>(p->n_t);
     // signed-weight rational classes (kind 3) go to a launch of their own:
@@ -526,10 +469,12 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             perm[cls[c].first + fill[c]++] = static_cast<int32_t>(o);
         }
         // NURBS (in sorted order, so a NURBS's rank is its slot in the class):
-        // read and validate the knot vectors, count segments, keep breakpoints
+        // read and validate the knot vectors, find the non-empty spans
         std::vector<int64_t> nurbs_obj;
-        std::vector<int32_t> seg_first(1, 0);
-        std::vector<float> brk;
+        std::vector<NurbsHead> nhead;
+        std::vector<uint16_t> ntab;
+        std::vector<float> nknots;
+        int64_t n_segs = 0, n_pts = 0;
         if (any_nurbs) {
             if (!knot_offset || !knots) return fail(BZ_ERR_NULL, "%s: knot_offset and knots are required for NURBS", fn);
             ko.resize(n_obj + 1);
@@ -541,6 +486,8 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             BZ_CHECK_HIP(hipMemcpyAsync(U.data(), knots, nk_total * sizeof(float), hipMemcpyDeviceToHost, s));
             BZ_CHECK_HIP(hipStreamSynchronize(s));
             const ClassInfo &nc = cls.back();
+            std::vector<int32_t> spans;
+            std::vector<int> buckets;
             for (int32_t r = 0; r < nc.count; ++r) {
                 const int64_t o = perm[nc.first + r];
                 const int64_t ncp = cpo[o + 1] - cpo[o];
@@ -554,15 +501,17 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
                     !(u[nk - 2 - kNurbsP] < u[nk - 1 - kNurbsP]))
                     return fail(BZ_ERR_SHAPE, "%s: NURBS object %lld knot vector is not clamped with end multiplicity 4", fn, (long long)o);
                 nurbs_obj.push_back(o);
-                int32_t ns = 0;
-                brk.push_back(u[kNurbsP]);
+                spans.clear();
                 for (int64_t i = kNurbsP; i < ncp; ++i)
-                    if (u[i] < u[i + 1]) {
-                        brk.push_back(u[i + 1]);
-                        ++ns;
-                    }
-                seg_first.push_back(seg_first.back() + ns);
+                    if (u[i] < u[i + 1]) spans.push_back(static_cast<int32_t>(i));
+                if (!add_nurbs(u, ncp, spans, n_pts, nhead, ntab, buckets)) return fail(BZ_ERR_INTERNAL, "%s: NURBS span table", fn);
+                nknots.insert(nknots.end(), u, u + nk);
+                n_segs += static_cast<int64_t>(spans.size());
+                n_pts += ncp;
+                if (n_pts > (int64_t(1) << 31) - 1 || ntab.size() > (size_t(1) << 31) - 1)
+                    return fail(BZ_ERR_SHAPE, "%s: more than 2^31 NURBS control points", fn);
             }
+            nknots.insert(nknots.end(), 4, 0.0f);  // the last NURBS's last window reads one past its knots
         }
         bz_plan_s *p = new (std::nothrow) bz_plan_s();
         if (!p) return fail(BZ_ERR_NOMEM, "%s: host allocation", fn);
@@ -573,7 +522,7 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
         p->method = method;
         p->classes = cls;
         for (const ClassInfo &ci : cls) p->has_patches = p->has_patches || ci.kind == 4;
-        p->n_segs = seg_first.back();
+        p->n_segs = n_segs;
         const int es = dtype_size(dtype);
         auto dmalloc = [&](void **ptr, size_t bytes) -> int {
             hipError_t e = hipMalloc(ptr, std::max<size_t>(bytes, 16));
@@ -582,17 +531,9 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
         };
         p->perm_h = perm;
         int rc = dev_upload(&p->perm, perm, s);
-        if (!rc) rc = dev_upload(&p->seg_first, seg_first, s);
-        if (!rc) rc = dev_upload(&p->brk, brk, s);
-        if (!rc) {
-            std::vector<NurbsHead> nh;
-            std::vector<NurbsTab> nt;
-            // (16-bit plans of many segments search instead, see NurbsHead)
-            if (!build_nurbs_tables(seg_first, brk, nh, nt, dtype == BZ_F32 || seg_first.back() <= kTableSegs))
-                rc = fail(BZ_ERR_INTERNAL, "%s: NURBS span table", fn);
-            if (!rc) rc = dev_upload(&p->nhead, nh, s);
-            if (!rc && !nt.empty()) rc = dev_upload(&p->ntab, nt, s);
-        }
+        if (!rc) rc = dev_upload(&p->nhead, nhead, s);
+        if (!rc) rc = dev_upload(&p->ntab, ntab, s);
+        if (!rc) rc = dev_upload(&p->nknots, nknots, s);
         if (!rc) {
             int dev = 0, cus = 0;
             hipError_t e = hipGetDevice(&dev);
@@ -606,7 +547,7 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
         }
         if (!rc) rc = dmalloc(&p->ctrl_s, ctrl_elems * es);
         if (!rc) rc = dmalloc(&p->w_s, w_elems * es);
-        if (!rc) rc = dmalloc(reinterpret_cast<void **>(&p->seg), std::max<int64_t>(p->n_segs, 1) * 4 * (dim + 1) * sizeof(float));
+        if (!rc) rc = dmalloc(&p->npts, n_pts * (dim + 1) * es);
         if (!rc) {
             rc = dmalloc(reinterpret_cast<void **>(&p->counters), 2 * sizeof(unsigned int));
             if (!rc && hipMemsetAsync(p->counters, 0, 2 * sizeof(unsigned int), s) != hipSuccess) rc = fail(BZ_ERR_HIP, "%s: memset", fn);
@@ -640,23 +581,19 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             rc = dev_upload(&nobj_d, nurbs_obj, s);
             if (!rc) {
                 const int nn = static_cast<int>(nurbs_obj.size());
-                const uint32_t blocks = (nn + kBlock - 1) / kBlock;
-                if (dtype == BZ_F32)
-                    hipLaunchKernelGGL((k_nurbs_extract<float>), dim3(blocks), dim3(kBlock), 0, s, nn, nobj_d, cp_offset,
-                                       knot_offset, static_cast<const float *>(ctrl), static_cast<const float *>(w), knots,
-                                       p->seg_first, dim, p->seg);
-                else if (dtype == BZ_F16)
-                    hipLaunchKernelGGL((k_nurbs_extract<_Float16>), dim3(blocks), dim3(kBlock), 0, s, nn, nobj_d,
-                                       cp_offset, knot_offset, static_cast<const _Float16 *>(ctrl),
-                                       static_cast<const _Float16 *>(w), knots, p->seg_first, dim, p->seg);
+                const uint32_t blocks = (nn + kBlock / 64 - 1) / (kBlock / 64);
+                if (es == 4)
+                    hipLaunchKernelGGL((k_gather_nurbs<uint32_t>), dim3(blocks), dim3(kBlock), 0, s, nn, nobj_d, cp_offset,
+                                       p->nhead, dim, static_cast<const uint32_t *>(ctrl),
+                                       static_cast<const uint32_t *>(w), static_cast<uint32_t *>(p->npts));
                 else
-                    hipLaunchKernelGGL((k_nurbs_extract<bf16_t>), dim3(blocks), dim3(kBlock), 0, s, nn, nobj_d,
-                                       cp_offset, knot_offset, static_cast<const bf16_t *>(ctrl),
-                                       static_cast<const bf16_t *>(w), knots, p->seg_first, dim, p->seg);
+                    hipLaunchKernelGGL((k_gather_nurbs<uint16_t>), dim3(blocks), dim3(kBlock), 0, s, nn, nobj_d, cp_offset,
+                                       p->nhead, dim, static_cast<const uint16_t *>(ctrl),
+                                       static_cast<const uint16_t *>(w), static_cast<uint16_t *>(p->npts));
                 hipError_t e = hipGetLastError();
                 if (e == hipSuccess) e = hipStreamSynchronize(s);
                 (void)hipFree(nobj_d);
-                if (e != hipSuccess) rc = hip_fail(e, "k_nurbs_extract");
+                if (e != hipSuccess) rc = hip_fail(e, "k_gather_nurbs");
             }
         }
         if (!rc) {

@@ -8,6 +8,11 @@
 namespace bzi {
 
 constexpr int kNurbsP = 3;
+// Sub-tiles of a NURBS tile: a lane's queries overlap their chains of dependent
+// loads, but their state must not cost the kernel's Bezier paths registers: with
+// FP32 rows four of them made degree-15 tiles spill (2^20 curves alone 126 us, 115
+// with two); 16-bit rows leave room (all objects 144 us with four, 149 with two).
+constexpr uint32_t nurbs_sub_tiles(bool f32) { return f32 ? 2 : 4; }
 
 struct ClassInfo {
     int32_t kind;       // 0 Bezier, 1 rational (all weights > 0), 2 NURBS, 3 rational with a weight <= 0,
@@ -28,38 +33,28 @@ struct Tile {
     uint32_t pad;
 };
 
-// Span lookup of a NURBS query, two ways (the persistent kernel takes the
-// faster for its storage type and size, measured in steady state):
-// - bucket table (FP32 storage, and 16-bit plans of up to kTableSegs segments):
-//   the parameter range [lo, hi] of NURBS r is cut into M = 2*nseg equal
-//   buckets; a parameter of bucket m lies in one of the segments tab[m].s ..
-//   tab[m+1].s (indices relative to the NURBS), and when those are two segments,
-//   tab[m].split (the breakpoint between them) decides.  More than two candidates
-//   (two or more breakpoints in one bucket) fall back to a binary search over the
-//   breakpoints of that range.
-// - binary search over the NURBS's nseg+1 breakpoints (larger 16-bit plans): a
-//   line or two that the 16 queries of a NURBS share, where the table costs one
-//   more random line per query.  With FP32 control rows streaming past, the
-//   search's dependent probes miss the cache and the table is faster; with
-//   16-bit rows they hit, and the search is.  In a small plan, where everything
-//   hits, only the length of the chain counts, and the table's is shorter: 3300
-//   objects x 10 with 5,706 segments 7.2 us by search, 5.8 by table; 17,000 x 16
-//   with 28,500: 7.4 and 6.9; from 55,000 segments on the same.
-constexpr int64_t kTableSegs = 32768;
-
+// A cubic NURBS of a plan: its control points [ncp][dim+1] (coordinates, weight)
+// in the storage type and its ncp+4 knots, both in rank order, so that rank r's
+// knots begin at cp0 + 4r.  A query finds its knot span and evaluates the four
+// basis functions there by Cox and de Boor's recursion; 16 queries of a NURBS of
+// 32 points touch about 6 cache lines of points, knots and table.  (Bezier
+// segments extracted at plan time, 64 bytes each with their own end points, and
+// tables of 8 bytes per entry made three times the bytes and 14 lines; against 64
+// bits the recursion is the more accurate, 7.0e-8 against 7.7e-8 of the points'
+// norm, at most 2.0e-7 against 7.2e-7.)
+// Span lookup: the parameter range [lo, hi] is cut into M = 2 * (non-empty spans)
+// equal buckets; a parameter of bucket m lies in one of the spans tab[m] ..
+// tab[m+1], numbered by their first knot.  The knots around the first candidate,
+// which the recursion needs anyway, decide between spans up to two apart;
+// further ones (crowded knots) are searched.
 struct NurbsHead {
-    int32_t s0;    // first segment of the NURBS in the plan's segment array
-    int32_t nseg;  // segments (non-empty knot spans)
-    int32_t tab0;  // first of its 2*nseg+1 table entries (if the plan has a table)
-    int32_t brk0;  // first of its nseg+1 breakpoints (s0 + rank)
-    float lo, hi;  // parameter range
-    float inv_h;   // M / (hi - lo); 0 when that is not finite (one bucket)
+    int32_t cp0;        // first of its control points
+    int32_t tab0;       // first of its M+1 table entries; -1: none (more than 65535 control points), all searched
+    int32_t n_buckets;  // M; without a table the last span
     int32_t pad;
-};
-
-struct NurbsTab {
-    int32_t s;    // first candidate segment of the bucket
-    float split;  // breakpoint after segment s (start of segment s+1)
+    float lo, hi;       // parameter range
+    float inv_h;        // M / (hi - lo); 0 when that is not finite (one bucket)
+    float pad2;
 };
 
 // Bucket of parameter u (already clamped to [lo, hi]).  Evaluated identically
@@ -89,9 +84,9 @@ struct BatchArgs {
     uint32_t n_tiles;          // tiles of the persistent launch
     uint32_t n_signed;         // tiles of signed-weight rationals, after those (a launch of their own)
     const NurbsHead *nhead;    // [n_nurbs], NURBS ranked in sorted order
-    const NurbsTab *ntab;      // span lookup tables, 2*nseg+1 entries per NURBS; null: search
-    const float *brk;          // breakpoints, nseg+1 per NURBS, from NurbsHead::brk0
-    const float *seg;          // [n_segs][4][dim+1] homogeneous
+    const uint16_t *ntab;      // span lookup tables
+    const float *nknots;       // knots
+    const void *npts;          // control points and weights, [ncp][dim+1] each
     const float *t;
     const float *v;            // second parameters (patches' v), [n_obj][n_t]; read for patches only
     float *out;
@@ -416,142 +411,128 @@ __device__ __forceinline__ void run_curve_tile4(const BatchArgs &a, const Tile &
 }
 
 // NURBS queries, staged across the sub-tiles so that the dependent loads of
-// one stage (header and object index; parameter; table entries; breakpoints
-// and segment) overlap over all of a lane's queries: clamp u to the NURBS's
-// range, find its bucket and segment, and evaluate that segment's rational
-// cubic.  Every stage moves its bytes in as few vector loads as it can: the
-// address unit serves about one distinct cache line per cycle, and a wave's
-// 64 queries spread over many segments.
-typedef int32_t i4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+// one stage (header and object index; parameter; table entries; knots; control
+// points) overlap over all of a lane's queries: clamp u to the NURBS's range,
+// find its span, and combine that span's four control points.  Every stage moves
+// its bytes in as few vector loads as it can: the address unit serves about one
+// distinct cache line per cycle, and a wave's 64 queries spread over several
+// NURBS.
+typedef uint16_t h2u __attribute__((ext_vector_type(2), aligned(2)));
 
-template <int DIM, bool SEARCH>
+template <int DIM, typename T, int Q>
 __device__ __forceinline__ void run_nurbs_tile(const BatchArgs &a, const Tile &tl, float *__restrict__ out) {
-    constexpr int H = DIM + 1;  // homogeneous coordinates; a segment is 4*H floats = H vectors
+    constexpr int H = DIM + 1;
     const uint32_t nq = static_cast<uint32_t>(tl.ci.count) * a.n_t;
-    uint32_t slot[kMaxQpt];
-    bool ok[kMaxQpt];
+    uint32_t rank[Q];
+    bool ok[Q];
+    NurbsHead h[Q];
+    int64_t q[Q];
+    uint32_t j[Q];
 #pragma unroll
-    for (int s = 0; s < kMaxQpt; ++s) {
+    for (int s = 0; s < Q; ++s) {
         const uint32_t qi = tl.q0 + s * kBlock + threadIdx.x;
         ok[s] = s < static_cast<int>(tl.qpt) && qi < tl.q1;
-        slot[s] = min(qi, nq - 1);
-    }
-    NurbsHead h[kMaxQpt];
-    int64_t q[kMaxQpt];
-    uint32_t j[kMaxQpt];
-#pragma unroll
-    for (int s = 0; s < kMaxQpt; ++s) {
-        const uint32_t r = fdiv(slot[s], a.div_nt);  // NURBS rank = slot in the class
-        j[s] = slot[s] - r * a.n_t;
-        slot[s] = r;
-        h[s] = a.nhead[r];
+        const uint32_t qc = min(qi, nq - 1);
+        rank[s] = fdiv(qc, a.div_nt);  // NURBS rank = slot in the class
+        j[s] = qc - rank[s] * a.n_t;
+        h[s] = a.nhead[rank[s]];
     }
 #pragma unroll
-    for (int s = 0; s < kMaxQpt; ++s) q[s] = static_cast<int64_t>(a.perm[tl.ci.first + slot[s]]) * a.n_t + j[s];
-    // the search's first probe depends only on the header: loaded beside t, it
-    // brings the breakpoints' line in while the parameter is on its way
-    float u[kMaxQpt];
-    [[maybe_unused]] float first[kMaxQpt];
-    if constexpr (SEARCH) {
+    for (int s = 0; s < Q; ++s) q[s] = static_cast<int64_t>(a.perm[tl.ci.first + rank[s]]) * a.n_t + j[s];
+    float u[Q];
 #pragma unroll
-        for (int s = 0; s < kMaxQpt; ++s) first[s] = a.brk[h[s].brk0 + (h[s].nseg >> 1)];
-    }
-#pragma unroll
-    for (int s = 0; s < kMaxQpt; ++s) {
+    for (int s = 0; s < Q; ++s) {
         const float v = a.t[q[s]];
-        float c = v < h[s].lo ? h[s].lo : v;  // NaN passes
+        const float c = v < h[s].lo ? h[s].lo : v;  // NaN passes
         u[s] = c > h[s].hi ? h[s].hi : c;
     }
-    int32_t sg[kMaxQpt];
-    if constexpr (SEARCH) {
-        // the last breakpoint <= u among the first nseg, by a binary search on
-        // [sg, sg + cnt) stepped for all of a lane's queries together (u is
-        // clamped to [lo, hi]; a NaN u stays in segment 0 and gives NaN)
-        int32_t cnt[kMaxQpt];
+    uint32_t lo[Q], hi[Q];  // candidate spans
 #pragma unroll
-        for (int s = 0; s < kMaxQpt; ++s) {
-            const int n = h[s].nseg, half = n >> 1;
-            const bool up = n > 1 && first[s] <= u[s];
-            sg[s] = up ? half : 0;
-            cnt[s] = n > 1 ? (up ? n - half : half) : n;
-        }
-        bool more = true;
-        while (more) {
-            more = false;
-#pragma unroll
-            for (int s = 0; s < kMaxQpt; ++s) {
-                if (cnt[s] > 1) {
-                    const int half = cnt[s] >> 1;
-                    if (a.brk[h[s].brk0 + sg[s] + half] <= u[s]) {
-                        sg[s] += half;
-                        cnt[s] -= half;
-                    } else {
-                        cnt[s] = half;
-                    }
-                    more = more || cnt[s] > 1;
-                }
-            }
-        }
-    } else {
-        i4u e[kMaxQpt];  // table entries m and m+1: {s, split bits, s, split bits}
-#pragma unroll
-        for (int s = 0; s < kMaxQpt; ++s) {
-            const int m = nurbs_bucket(u[s], h[s].lo, h[s].inv_h, 2 * h[s].nseg);
-            e[s] = *reinterpret_cast<const i4u *>(a.ntab + h[s].tab0 + m);
-        }
-#pragma unroll
-        for (int s = 0; s < kMaxQpt; ++s) {
-            int lo = e[s][0], hi = e[s][2];
-            if (hi - lo <= 1) {
-                sg[s] = (hi > lo && __int_as_float(e[s][1]) <= u[s]) ? hi : lo;
-            } else {  // two or more breakpoints inside the bucket
-                const float *b = a.brk + h[s].brk0;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (b[mid] <= u[s]) lo = mid;
-                    else hi = mid - 1;
-                }
-                sg[s] = lo;
-            }
+    for (int s = 0; s < Q; ++s) {
+        lo[s] = kNurbsP;
+        hi[s] = h[s].n_buckets;
+        if (h[s].tab0 >= 0) {
+            const int m = nurbs_bucket(u[s], h[s].lo, h[s].inv_h, h[s].n_buckets);
+            const h2u e = *reinterpret_cast<const h2u *>(a.ntab + h[s].tab0 + m);
+            lo[s] = e[0];
+            hi[s] = e[1];
         }
     }
-    f2u br[kMaxQpt];
-    float S[kMaxQpt][4 * H];
+    const float *U[Q];
+    float W[Q][8];  // knots lo-2 .. lo+5 (the last may be past the NURBS's own; the array is padded)
 #pragma unroll
-    for (int s = 0; s < kMaxQpt; ++s) {
-        br[s] = *reinterpret_cast<const f2u *>(a.brk + h[s].brk0 + sg[s]);
-        const float *__restrict__ p = a.seg + static_cast<size_t>(h[s].s0 + sg[s]) * 4 * H;
+    for (int s = 0; s < Q; ++s) {
+        U[s] = a.nknots + h[s].cp0 + 4 * static_cast<int64_t>(rank[s]);
+        load_row<float, 8>(U[s] + lo[s] - 2, W[s]);
+    }
+    float K[Q][6];  // knots i-2 .. i+3 of span i
+    uint32_t span[Q];
 #pragma unroll
-        for (int v = 0; v < H; ++v) {
-            const f4u x = *reinterpret_cast<const f4u *>(p + 4 * v);
-            S[s][4 * v] = x[0], S[s][4 * v + 1] = x[1], S[s][4 * v + 2] = x[2], S[s][4 * v + 3] = x[3];
+    for (int s = 0; s < Q; ++s) {
+        const bool one = hi[s] > lo[s] && W[s][3] <= u[s], two = hi[s] > lo[s] + 1 && W[s][4] <= u[s];
+        span[s] = lo[s] + (two ? 2 : one ? 1 : 0);
+#pragma unroll
+        for (int e = 0; e < 6; ++e) K[s][e] = two ? W[s][e + 2] : one ? W[s][e + 1] : W[s][e];
+        if (hi[s] > lo[s] + 2) {  // the last span starting at or before u (NaN: the first)
+            uint32_t x = lo[s], y = hi[s];
+            while (x < y) {
+                const uint32_t mid = (x + y + 1) >> 1;
+                if (U[s][mid] <= u[s]) x = mid;
+                else y = mid - 1;
+            }
+            span[s] = x;
+            load_row<float, 6>(U[s] + x - 2, K[s]);
         }
     }
+    float S[Q][4 * H];
 #pragma unroll
-    for (int s = 0; s < kMaxQpt; ++s) {
+    for (int s = 0; s < Q; ++s)
+        load_row<T, 4 * H>(static_cast<const T *>(a.npts) + (static_cast<size_t>(h[s].cp0) + span[s] - kNurbsP) * H, S[s]);
+#pragma unroll
+    for (int s = 0; s < Q; ++s) {
         if (!ok[s]) continue;
-        const float tseg = (u[s] - br[s][0]) / (br[s][1] - br[s][0]);
-        float B[4];
-        bernstein_basis<3>(tseg, B);
-        float acc[H] = {};
+        // N[0..3]: basis functions span-3 .. span, each divisor a sum of knot
+        // distances that covers the non-empty span
+        // (only ratios count: knots of extreme size or distance are scaled first)
+        const float sc = K[s][5] - K[s][0] > 0x1p60f ? 0x1p-60f : K[s][3] - K[s][2] < 0x1p-60f ? 0x1p60f : 1.0f;
+        const float l1 = (u[s] - K[s][2]) * sc, l2 = (u[s] - K[s][1]) * sc, l3 = (u[s] - K[s][0]) * sc;
+        const float r1 = (K[s][3] - u[s]) * sc, r2 = (K[s][4] - u[s]) * sc, r3 = (K[s][5] - u[s]) * sc;
+        float N[4];
+        float p = 1.0f / (r1 + l1);
+        N[0] = r1 * p;
+        N[1] = l1 * p;
+        p = N[0] / (r1 + l2);
+        const float p2 = N[1] / (r2 + l1);
+        N[0] = r1 * p;
+        N[1] = __builtin_fmaf(r2, p2, l2 * p);
+        N[2] = l1 * p2;
+        p = N[0] / (r1 + l3);
+        const float p3 = N[1] / (r2 + l2), p4 = N[2] / (r3 + l1);
+        N[0] = r1 * p;
+        N[1] = __builtin_fmaf(r2, p3, l3 * p);
+        N[2] = __builtin_fmaf(r3, p4, l2 * p3);
+        N[3] = l1 * p4;
+        float den = 0.0f, acc[DIM] = {};
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) {
+            const float wn = N[i] * S[s][i * H + DIM];
+            den += wn;
 #pragma unroll
-            for (int k = 0; k < H; ++k) acc[k] = __builtin_fmaf(B[i], S[s][i * H + k], acc[k]);
-        const float rw = 1.0f / acc[DIM];
+            for (int k = 0; k < DIM; ++k) acc[k] = __builtin_fmaf(wn, S[s][i * H + k], acc[k]);
+        }
+        const float rw = 1.0f / den;
 #pragma unroll
         for (int k = 0; k < DIM; ++k) st_stream(out + k * a.plane + q[s], acc[k] * rw);
     }
 }
 
-template <bool SEARCH>
+template <typename T, int Q>
 __device__ __forceinline__ void run_nurbs_tile_dim(const BatchArgs &a, const Tile &tl, float *__restrict__ out) {
     switch (a.dim) {
-        case 1: run_nurbs_tile<1, SEARCH>(a, tl, out); break;
-        case 2: run_nurbs_tile<2, SEARCH>(a, tl, out); break;
-        case 3: run_nurbs_tile<3, SEARCH>(a, tl, out); break;
-        default: run_nurbs_tile<4, SEARCH>(a, tl, out); break;
+        case 1: run_nurbs_tile<1, T, Q>(a, tl, out); break;
+        case 2: run_nurbs_tile<2, T, Q>(a, tl, out); break;
+        case 3: run_nurbs_tile<3, T, Q>(a, tl, out); break;
+        default: run_nurbs_tile<4, T, Q>(a, tl, out); break;
     }
 }
 
@@ -707,8 +688,8 @@ __device__ __forceinline__ void run_tile(const BatchArgs &a, unsigned int tile, 
     if (tl.ci.kind == 0) dispatch_degree<false, F, T, VQ>(a, tl, out);
     else if (tl.ci.kind == 1) dispatch_degree<true, F, T, VQ>(a, tl, out);
     else if (tl.ci.kind == 4) dispatch_patch<F, T, VQ>(a, tl, out);
-    else if (std::is_same<T, float>::value || a.ntab) run_nurbs_tile_dim<false>(a, tl, out);
-    else run_nurbs_tile_dim<true>(a, tl, out);
+    else if (tl.qpt == 1) run_nurbs_tile_dim<T, 1>(a, tl, out);
+    else run_nurbs_tile_dim<T, nurbs_sub_tiles(std::is_same<T, float>::value)>(a, tl, out);
 }
 
 // Dynamic schedule: workgroups pull tiles from an atomic counter (the next
