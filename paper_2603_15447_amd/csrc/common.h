@@ -17,6 +17,16 @@ namespace bzi {
 constexpr int kMaxDegree = 15;
 constexpr int kMaxDim = 4;
 constexpr int kBlock = 256;
+// Queries per thread of the chain evaluators.  They are bound by the line
+// fills of their gather, so by how many wavefronts keep windows in flight: two
+// queries cost half the registers of four and leave twice the wavefronts.
+// 2^24 random 3D queries, four -> two: a grid of 2^17 segments 173 -> 123 us,
+// its tiles 159 -> 132, cubic tiles 246 -> 208; 2^13 segments 165 -> 114,
+// 142 -> 107, 174 -> 148.  From 2^20 segments on, where every query fills its
+// line from beyond the L2, both take the same within 1 %; one query per thread
+// was 97, 138 and 299 us at 2^10, 2^17 and 2^20 segments' tiles, two 90, 132
+// and 299.
+constexpr int kChainQueries = 2;
 
 // ------------------------------------------------------------------ host
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kBlock) void k_piecewise_cubic_eval(const float *__
 template <int DIM>
 int launch_cubic_eval(const float *grid, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                       hipStream_t s) {
-    constexpr int Q = 4;
+    constexpr int Q = kChainQueries;
     const uint32_t blocks = (nq + kBlock * Q - 1) / (kBlock * Q);
     hipLaunchKernelGGL((k_piecewise_cubic_eval<DIM, Q>), dim3(blocks), dim3(kBlock), 0, s, grid, n_seg, T, nq, out,
                        plane);
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kBlock) void k_piecewise_cubic_eval_tiled(const flo
 template <int DIM>
 int launch_cubic_eval_tiled(const float *tiles, uint32_t n_seg, const float *T, uint32_t nq, float *out,
                             int64_t plane, hipStream_t s) {
-    constexpr int Q = 4;
+    constexpr int Q = kChainQueries;
     const uint32_t blocks = (nq + kBlock * Q - 1) / (kBlock * Q);
     hipLaunchKernelGGL((k_piecewise_cubic_eval_tiled<DIM, Q>), dim3(blocks), dim3(kBlock), 0, s, tiles, n_seg, T, nq,
                        out, plane);

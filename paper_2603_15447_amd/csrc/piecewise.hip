@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kBlock) void k_piecewise_eval_tiled(const float *__
 template <int DIM>
 int launch_eval_tiled(const float *tiles, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                       hipStream_t s) {
-    constexpr int Q = 4;
+    constexpr int Q = kChainQueries;
     const uint32_t per_block = kBlock * Q;
     const uint32_t blocks = (nq + per_block - 1) / per_block;
     hipLaunchKernelGGL((k_piecewise_eval_tiled<DIM, Q>), dim3(blocks), dim3(kBlock), 0, s, tiles, n_seg, T, nq, out,
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_piecewise_eval_tiled16(const uint16_
 template <int DIM, typename H>
 int launch_eval_tiled16(const uint16_t *tiles, uint32_t n_seg, const float *Tp, uint32_t nq, float *out, int64_t plane,
                         hipStream_t s) {
-    constexpr int Q = 4;
+    constexpr int Q = kChainQueries;
     const uint32_t per_block = kBlock * Q;
     const uint32_t blocks = (nq + per_block - 1) / per_block;
     hipLaunchKernelGGL((k_piecewise_eval_tiled16<DIM, H, Q>), dim3(blocks), dim3(kBlock), 0, s, tiles, n_seg, Tp, nq,
@@ -340,12 +340,12 @@ int eval_tiled16_dim(int dim, const uint16_t *tiles, uint32_t ns, const float *T
     }
 }
 
-// Queries per thread; BZ_PIECEWISE_QPT (1, 2, 4 or 8) overrides the default.
+// Queries per thread; BZ_PIECEWISE_QPT (1, 2, 4 or 8) overrides kChainQueries.
 int piecewise_qpt() {
     static const int q = [] {
         const char *e = getenv("BZ_PIECEWISE_QPT");
-        const int v = e ? atoi(e) : 4;
-        return (v == 1 || v == 2 || v == 4 || v == 8) ? v : 4;
+        const int v = e ? atoi(e) : kChainQueries;
+        return (v == 1 || v == 2 || v == 4 || v == 8) ? v : kChainQueries;
     }();
     return q;
 }

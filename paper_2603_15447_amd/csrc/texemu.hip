@@ -288,7 +288,7 @@ int tex_texels_rt(int degree, int mode) {
 template <int DIM, bool TILED>
 int launch_chain_texemu(const float *grid, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                         int F, int rnd, hipStream_t s) {
-    constexpr int Q = 4;
+    constexpr int Q = kChainQueries;
     const uint32_t blocks = (nq + kBlock * Q - 1) / (kBlock * Q);
     hipLaunchKernelGGL((k_piecewise_texemu<DIM, Q, TILED>), dim3(blocks), dim3(kBlock), 0, s, grid, n_seg, T, nq, out,
                        plane, F, rnd);
