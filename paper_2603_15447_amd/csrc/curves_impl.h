@@ -411,7 +411,8 @@ __global__ __launch_bounds__(kBlock) void k_curves_mixed(CurveArgs a) {
     for (int k = 0; k < DIM; ++k) {
         float *__restrict__ oc = out + k * a.plane;
         const uint32_t sc = line_offset(oc), lo = at > sc ? 0 : sc - at;  // plane queries [at - sc + lo, ...)
-        const uint32_t n_own = min(static_cast<uint32_t>(a.chunk), a.nq + sc - at);
+        // (none in the last workgroup where the plane's end lies before its part)
+        const uint32_t n_own = a.nq + sc > at ? min(static_cast<uint32_t>(a.chunk), a.nq + sc - at) : 0;
         float *__restrict__ to = oc + at - sc;
         const float *__restrict__ from = buf + k * pitch + static_cast<int>(at - sc - first);
         for (uint32_t p = threadIdx.x; p < n_own; p += kBlock)

@@ -71,3 +71,27 @@ def test_division_ranges(orc):
     t = rng.random((n, nt)).astype(np.float32)
     got = host(bz.eval_rational(to_dev(ctrl), to_dev(w), to_dev(t), "bernstein"))
     assert bbox_err(got, orc.rational_eval(ctrl, w, t, per_object=True), extents(ctrl), nt) <= TOL_F32
+
+
+@pytest.mark.parametrize("n,nt", [(40, 33), (31, 65), (4039, 65), (15932, 33)])
+@pytest.mark.parametrize("rational", [False, True])
+def test_planes_that_end_before_the_last_part(orc, n, nt, rational):
+    """Planes that don't lie alike and end up to 31 queries before the last
+    workgroup's part of them begins: that part is empty, in the plane's
+    neighbour nothing is written."""
+    if rational:
+        ctrl, w, t = bz_synth.rational_curves(n, 3, 3, nt, seed=n)
+        ref = orc.rational_eval(ctrl, w, t, per_object=True)
+    else:
+        ctrl, t = bz_synth.random_curves(n, 3, 3, nt, seed=n)
+        ref = orc.bezier_decasteljau(ctrl, t, per_object=True)
+    cd, td, m = to_dev(ctrl), to_dev(t), 3 * n * nt
+    for shift in (0, 7):
+        flat = torch.full((m + 2048,), -7.0, device="cuda")
+        out = flat[shift:shift + m].view(3, n * nt)
+        if rational:
+            bz.eval_rational(cd, to_dev(w), td, "bernstein", out=out)
+        else:
+            bz.eval_bezier(cd, td, "bernstein", out=out)
+        assert bbox_err(host(out), ref, extents(ctrl), nt) <= TOL_F32, shift
+        assert bool((flat[:shift] == -7.0).all()) and bool((flat[shift + m:] == -7.0).all()), shift
