@@ -7,8 +7,10 @@
 //                  the v basis once per grid column (isoline coefficients
 //                  R_i(v_b), shared through LDS with the u basis of its rows),
 //                  then du+1 FMAs per coordinate and point.
-//  k_tensor_points one object per wavefront, random (u,v[,w]) per query,
-//                  4 queries per lane, separable contraction w -> v -> u.
+//  k_tensor_points_staged  surfaces at random (u,v) per query: a run of queries
+//                  per workgroup, their objects' nets in LDS, v -> u per lane.
+//  k_tensor_points one object per wavefront, random (u,v,w) per query, 4
+//                  queries per lane, separable contraction w -> v -> u.
 //  k_tensor_points_mfma  volumes of degrees 2 and 3 likewise, w contracted on the
 //                  matrix cores.
 #pragma once
@@ -315,12 +317,10 @@ GridArgs grid_args(int nu, int nv, int64_t n_obj, int64_t plane) {
 }
 
 // ------------------------------------------------------------------ VALU points
-// One object per wavefront, 4 queries per lane at a time: the object's
+// Volumes, one object per wavefront, 4 queries per lane at a time: the object's
 // control points are wave-uniform (scalar loads into SGPRs) and each one
 // feeds the FMAs of 4 queries.  Separable contraction w -> v -> u.  An
 // object's queries go to waves_per_obj wavefronts, of per_wave * 64 * kPtsQ each.
-// (Two queries per lane for objects of up to 128: 31 us for 30000 bicubics x 65,
-// against 23.5 with four, half of them idle.)
 constexpr int kPtsQ = 4;
 
 template <int DU, int DV, int DW, int DIM, typename T, int BASIS>
@@ -329,7 +329,6 @@ __global__ __launch_bounds__(kBlock) void k_tensor_points(const T *__restrict__ 
                                                           int per_wave, float *__restrict__ out, int64_t plane,
                                                           int64_t o0) {
     constexpr int NCP = (DU + 1) * (DV + 1) * (DW + 1);
-    constexpr int NPAR = DW > 0 ? 3 : 2;
     const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
     const uint32_t o = w / waves_per_obj;
     if (o >= n_obj) return;
@@ -346,11 +345,10 @@ __global__ __launch_bounds__(kBlock) void k_tensor_points(const T *__restrict__ 
             const int64_t j = j0 + s * 64 + lane;
             ok[s] = j < n_per;
             q[s] = (o0 + o) * n_per + (ok[s] ? j : n_per - 1);
-            const float *__restrict__ p = uvw + q[s] * NPAR;
+            const float *__restrict__ p = uvw + q[s] * 3;
             basis_at<DU, BASIS>(p[0], Bu[s]);
             basis_at<DV, BASIS>(p[1], Bv[s]);
-            if constexpr (DW > 0) basis_at<DW, BASIS>(p[2], Bw[s]);
-            else Bw[s][0] = 1.0f;
+            basis_at<DW, BASIS>(p[2], Bw[s]);
         }
         // One (coordinate, i) slab of (DV+1)(DW+1) coefficients at a time: the
         // slab loop is not unrolled, so the scalar loads of one slab are in
@@ -382,6 +380,113 @@ __global__ __launch_bounds__(kBlock) void k_tensor_points(const T *__restrict__ 
             for (int s = 0; s < kPtsQ; ++s)
                 if (ok[s]) st_stream(out + c * plane + q[s], acc[s]);
         }
+    }
+}
+
+// ------------------------------------------------------------------ staged points
+// Surfaces: a workgroup takes a run of `chunk` queries, whichever objects they
+// belong to, and stages those objects' nets in LDS; each lane then reads its own
+// object's net (a wavefront's lanes share few objects, whose reads are
+// broadcasts) and contracts v and u, in k_tensor_points' order.  Points of
+// misaligned planes go through LDS to be stored as whole lines, as in
+// k_curves_mixed.
+// Bound by the 20 bytes per query and by the LDS reads of the net (12 of 16
+// bytes for a bicubic in 3D).  A wavefront per object left its lanes idle below
+// 256 points and paid a chain of scalar loads per object; a single large object
+// was one wavefront's.  2^22 points of 3D bicubics, wavefront per object -> staged:
+// 32 points each 71-91 -> 19.6 us, 64 38-42 -> 17.1, 100 28 -> 19, 256 16.1 -> 14.8
+// (5.7 TB/s), 333 21 -> 16.7, 1000 17-20 -> 15.2, 1 each 2235 -> 167.
+struct PtsArgs {
+    int64_t q0;     // the first query's place in uvw and in a plane
+    int64_t plane;
+    uint32_t nq;
+    int chunk;      // queries per workgroup
+    int slots;      // objects it may touch
+    bool same;      // whether the planes' lines begin at the same queries
+    FastDiv div_n;  // queries per object
+};
+
+template <int DU, int DV, int DIM>
+struct PtsGeom {
+    static constexpr int NCP = (DU + 1) * (DV + 1);
+    static constexpr int PAD = (NCP + 3) / 4 * 4;  // floats per coordinate: whole 16-byte vectors
+    static constexpr int OBJ = DIM * PAD + 4;      // (+ 4: neighbouring objects in other banks)
+};
+
+template <int DU, int DV, int DIM, typename T, int BASIS>
+__global__ __launch_bounds__(kBlock) void k_tensor_points_staged(const T *__restrict__ ctrl, const float *__restrict__ uvw,
+                                                                 PtsArgs a, float *__restrict__ out) {
+    using G = PtsGeom<DU, DV, DIM>;
+    constexpr int NCP = G::NCP, PAD = G::PAD;
+    extern __shared__ __align__(16) float lds[];
+    out += a.q0;
+    const uint32_t at = blockIdx.x * a.chunk;
+    const uint32_t sh = a.same ? line_offset(out) : 31u;
+    const uint32_t first = at > sh ? at - sh : 0;
+    const uint32_t end = min(a.nq, at + a.chunk - (a.same ? sh : 0u));
+    const int n = static_cast<int>(end - first);
+    if (n <= 0) return;
+    const uint32_t o_lo = fdiv(first, a.div_n), s0 = first - o_lo * a.div_n.d;
+    const int n_o = static_cast<int>(fdiv(s0 + n - 1, a.div_n)) + 1;
+    const float *__restrict__ uv = uvw + (a.q0 + first) * 2;
+    float u_next = uv[min(static_cast<int>(threadIdx.x), n - 1) * 2];  // on its way while the nets are staged
+    float v_next = uv[min(static_cast<int>(threadIdx.x), n - 1) * 2 + 1];
+    const T *__restrict__ P = ctrl + static_cast<size_t>(o_lo) * DIM * NCP;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < n_o * DIM * NCP; e += kBlock) {
+        const int r = e / NCP, i = e - r * NCP;
+        const int k = r / DIM, c = r - k * DIM;
+        lds[k * G::OBJ + c * PAD + i] = to_f32<T>(P[e]);
+    }
+    __syncthreads();
+    float *__restrict__ buf = lds + a.slots * G::OBJ;  // [DIM][chunk + 32] unless the planes lie alike
+    const int pitch = a.chunk + 32;
+    auto points = [&](auto same) {
+#pragma unroll 1
+        for (int p = threadIdx.x; p < n; p += kBlock) {
+            float Bu[DU + 1], Bv[DV + 1];
+            basis_at<DU, BASIS>(u_next, Bu);
+            basis_at<DV, BASIS>(v_next, Bv);
+            u_next = uv[min(p + kBlock, n - 1) * 2];
+            v_next = uv[min(p + kBlock, n - 1) * 2 + 1];
+            const float *__restrict__ net = lds + fdiv(s0 + p, a.div_n) * G::OBJ;
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                float x[PAD];
+#pragma unroll
+                for (int e = 0; e < PAD; e += 4) {
+                    const float4 f = *reinterpret_cast<const float4 *>(net + c * PAD + e);
+                    x[e] = f.x, x[e + 1] = f.y, x[e + 2] = f.z, x[e + 3] = f.w;
+                }
+                float acc = 0.0f;
+#pragma unroll
+                for (int i = 0; i <= DU; ++i) {
+                    float R = 0.0f;
+#pragma unroll
+                    for (int j = 0; j <= DV; ++j) R = __builtin_fmaf(Bv[j], x[i * (DV + 1) + j], R);
+                    acc = __builtin_fmaf(Bu[i], R, acc);
+                }
+                if constexpr (decltype(same)::value) st_stream(at_lane(out + c * a.plane + first, p), acc);
+                else buf[c * pitch + p] = acc;
+            }
+        }
+    };
+    if (a.same) {
+        points(std::true_type{});
+        return;
+    }
+    points(std::false_type{});
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+        float *__restrict__ oc = out + c * a.plane;
+        const uint32_t sc = line_offset(oc), lo = at > sc ? 0 : sc - at;  // plane queries [at - sc + lo, ...)
+        // (none in the last workgroup where the plane's end lies before its part)
+        const uint32_t n_own = a.nq + sc > at ? min(static_cast<uint32_t>(a.chunk), a.nq + sc - at) : 0;
+        float *__restrict__ to = oc + at - sc;
+        const float *__restrict__ from = buf + c * pitch + static_cast<int>(at - sc - first);
+        for (uint32_t p = threadIdx.x; p < n_own; p += kBlock)
+            if (p >= lo) st_stream(at_lane(to, p), from[p]);
     }
 }
 
@@ -589,14 +694,47 @@ template <int BASIS, int DU, int DV, int DW>
 constexpr bool kPointsMfma = BASIS == kBasisBernstein && DW >= 2 && DU <= 3 && DV <= 3 && DW <= 3 &&
                              (DU + 1) * (DV + 1) * (DW + 1) >= 27;
 
+// Surfaces' points: chunks of 1024 queries, fewer in calls too small to give
+// every CU two workgroups and where the nets of so many would not leave a CU
+// four; 128 queries' nets fit a workgroup's 64 KB at any degree, even with one
+// point each.  At most 2^30 queries per launch: whole objects, or pieces of one.
+template <typename T, int BASIS, int DU, int DV, int DIM>
+void launch_pts_staged(const T *ctrl, const float *uvw, int64_t n_per, float *out, int64_t plane, int64_t o0,
+                       int64_t n_obj, hipStream_t s) {
+    using G = PtsGeom<DU, DV, DIM>;
+    static_assert(128 * G::OBJ <= 16384 && 127 * G::OBJ + DIM * 128 <= 16384, "128 queries' nets fit 64 KB");
+    constexpr int64_t kMost = int64_t(1) << 30;
+    const int64_t per = std::min(n_per, kMost), step = kMost / per;
+    PtsArgs a;
+    a.plane = plane;
+    a.same = DIM == 1 || plane % 16 == 0;
+    for (int64_t i = 0; i < n_obj; i += step)
+        for (int64_t j = 0; j < n_per; j += per) {
+            const int64_t piece = std::min(per, n_per - j);
+            a.q0 = (o0 + i) * n_per + j;
+            a.nq = static_cast<uint32_t>(std::min(step, n_obj - i) * piece);
+            a.div_n = make_fastdiv(static_cast<uint32_t>(piece));
+            size_t floats = 0;
+            for (int want = a.nq >= 1024u * 512 ? 1024 : a.nq >= 512u * 512 ? 512 : 256;; want /= 2) {
+                a.chunk = a.same ? want : want - 32;  // with the planes' own first queries: whole threads
+                const int64_t span = a.chunk + (a.same ? 0 : 31);
+                a.slots = static_cast<int>((span + piece - 2) / piece + 1);
+                floats = static_cast<size_t>(a.slots) * G::OBJ + (a.same ? 0 : DIM * (a.chunk + 32));
+                if (floats <= 10240 || want == 128) break;
+            }
+            const uint32_t blocks = (a.nq + 31 + a.chunk - 1) / a.chunk;
+            hipLaunchKernelGGL((k_tensor_points_staged<DU, DV, DIM, T, BASIS>), dim3(blocks), dim3(kBlock),
+                               floats * sizeof(float), s, ctrl + i * DIM * G::NCP, uvw, a, out);
+        }
+}
+
 template <typename T, int BASIS, int DU, int DV, int DW, int DIM>
-void launch_pts4(const void *ctrl, const float *uvw, int64_t n_per, float *out, int64_t plane, int64_t o0,
+void launch_pts4(const T *ctrl, const float *uvw, int64_t n_per, float *out, int64_t plane, int64_t o0,
                  uint32_t n_obj, hipStream_t s) {
     constexpr bool MFMA = kPointsMfma<BASIS, DU, DV, DW>;
     // pieces of an object's queries, 64 times the queries per lane; up to 4 x 64
     // queries per wavefront while that leaves 16 wavefronts per CU (626 tricubics
-    // x 604: 12.5 us with a wavefront per object, 6.2 so; 200 bicubics x 600: 7.8
-    // and 4.6)
+    // x 604: 12.5 us with a wavefront per object, 6.2 so)
     const int q = MFMA ? 1 : kPtsQ;
     const int64_t pieces = (n_per + 64 * q - 1) / (64 * q);
     const int64_t most = MFMA ? 4 : 1;
@@ -608,7 +746,7 @@ void launch_pts4(const void *ctrl, const float *uvw, int64_t n_per, float *out, 
         const uint32_t no = static_cast<uint32_t>(std::min<int64_t>(step, n_obj - i));
         const uint64_t waves = static_cast<uint64_t>(no) * wpo;
         const dim3 blocks(static_cast<uint32_t>((waves + kBlock / 64 - 1) / (kBlock / 64)));
-        const T *p = static_cast<const T *>(ctrl) + i * DIM * (DU + 1) * (DV + 1) * (DW + 1);
+        const T *p = ctrl + i * DIM * (DU + 1) * (DV + 1) * (DW + 1);
         const int pw = static_cast<int>(per);
         if constexpr (MFMA)
             hipLaunchKernelGGL((k_tensor_points_mfma<DU, DV, DW, DIM, T>), blocks, dim3(kBlock), 0, s, p, uvw, n_per, no,
@@ -619,14 +757,22 @@ void launch_pts4(const void *ctrl, const float *uvw, int64_t n_per, float *out, 
     }
 }
 
+template <typename T, int BASIS, int DU, int DV, int DW, int DIM>
+void launch_pts_dim(const T *ctrl, const float *uvw, int64_t n_per, float *out, int64_t plane, int64_t o0,
+                    uint32_t n_obj, hipStream_t s) {
+    if constexpr (DW == 0) launch_pts_staged<T, BASIS, DU, DV, DIM>(ctrl, uvw, n_per, out, plane, o0, n_obj, s);
+    else launch_pts4<T, BASIS, DU, DV, DW, DIM>(ctrl, uvw, n_per, out, plane, o0, n_obj, s);
+}
+
 template <typename T, int BASIS, int DU, int DV, int DW>
 int launch_pts3(int dim, const void *ctrl, const float *uvw, int64_t n_per, float *out, int64_t plane, int64_t o0,
                 uint32_t n_obj, hipStream_t s) {
+    const T *p = static_cast<const T *>(ctrl);
     switch (dim) {
-        case 1: launch_pts4<T, BASIS, DU, DV, DW, 1>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
-        case 2: launch_pts4<T, BASIS, DU, DV, DW, 2>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
-        case 3: launch_pts4<T, BASIS, DU, DV, DW, 3>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
-        default: launch_pts4<T, BASIS, DU, DV, DW, 4>(ctrl, uvw, n_per, out, plane, o0, n_obj, s); break;
+        case 1: launch_pts_dim<T, BASIS, DU, DV, DW, 1>(p, uvw, n_per, out, plane, o0, n_obj, s); break;
+        case 2: launch_pts_dim<T, BASIS, DU, DV, DW, 2>(p, uvw, n_per, out, plane, o0, n_obj, s); break;
+        case 3: launch_pts_dim<T, BASIS, DU, DV, DW, 3>(p, uvw, n_per, out, plane, o0, n_obj, s); break;
+        default: launch_pts_dim<T, BASIS, DU, DV, DW, 4>(p, uvw, n_per, out, plane, o0, n_obj, s); break;
     }
     return BZ_OK;
 }
