@@ -95,3 +95,25 @@ def test_planes_that_end_before_the_last_part(orc, n, nt, rational):
             bz.eval_bezier(cd, td, "bernstein", out=out)
         assert bbox_err(host(out), ref, extents(ctrl), nt) <= TOL_F32, shift
         assert bool((flat[:shift] == -7.0).all()) and bool((flat[shift + m:] == -7.0).all()), shift
+
+
+@pytest.mark.parametrize("nt", [9, 64, 100])
+def test_seiler_terms_of_weighted_points_are_rounded_once(nt):
+    """Quadratics whose end points a, -3 a cancel at t = 1/4 and whose inner
+    product p w = -a + r rounds to -a: the point there is (3/8) r over the weight
+    sum, if the product enters the terms unrounded, and else zero.  All steps
+    before the weight sum's four roundings and the quotient's are exact but one."""
+    rng = np.random.default_rng(nt)
+    n = 500
+    p, w1 = (rng.uniform(0.5, 2.0, n).astype(np.float32) for _ in range(2))
+    a = -(p * w1)
+    r = p.astype(np.float64) * w1 + a.astype(np.float64)
+    ctrl = np.stack([a, p, -3.0 * a], axis=1)[:, None].repeat(3, axis=1)
+    ctrl[:, :, 1] = p[:, None]
+    w = np.stack([np.ones(n), w1, np.ones(n)], axis=1).astype(np.float32)
+    exact = -3.0 * a.astype(np.float64) == (np.float32(-3.0) * a).astype(np.float64)  # (3 a needs at most 24 bits)
+    t = np.full((n, nt), 0.25, np.float32)
+    got = host(bz.eval_rational(to_dev(ctrl.astype(np.float32)), to_dev(w), to_dev(t), "seiler")).reshape(3, n, nt)
+    ref = 0.375 * r / (1.0 + 0.375 * (w1.astype(np.float64) - 1.0))
+    assert exact.sum() > n // 4 and (r[exact] != 0).sum() > n // 8
+    assert np.abs(got - ref[:, None])[:, exact].max() <= 8 * 2.0 ** -24 * np.abs(ref).max()
