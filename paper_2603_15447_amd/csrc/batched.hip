@@ -143,9 +143,19 @@ struct Layout {
 // with 4 x 4, 138 with 4 x 1; 400,000 x 12: 82 and 68), and of longer ones two
 // sub-tiles do better than four (300,000 x 24: 64 us, 72 with four or with one
 // query per lane).
-Layout default_layout(const std::vector<ClassInfo> &cls, int64_t n_t, uint32_t cus) {
+// De Casteljau is quadratic in the degree: 4 x 4 queries of degree 15 in turn are a
+// long tail until every CU has 16 tiles of 2048 queries, and 2 x 4 suffice from
+// there on (34,800 curves and NURBS x 16, FP32: 34 us with 4 x 4, 14 with 4 x 1;
+// 278,500: 68 and 60; 1.1 million: 221 with 4 x 4, 213 with 4 x 1, 201 with 2 x 4).
+Layout default_layout(const std::vector<ClassInfo> &cls, int method, int64_t n_t, uint32_t cus) {
     std::vector<Layout> choices;
-    if (n_t % 16 == 0) choices = {{4, 4, 1u << 17}, {4, 1, 1u << 17}, {2, 1, 1u << 17}, {1, 1, 1u << 17}};
+    if (method == BZ_DECASTELJAU && n_t % 4 == 0 && n_t >= 16) {
+        const uint32_t win = n_t % 16 == 0 ? 1u << 17 : 1u << 15;
+        int64_t queries = 0;
+        for (const ClassInfo &ci : cls) queries += ci.count * n_t;
+        if (queries >= static_cast<int64_t>(cus) * 16 * 2048) return {2, 4, win};
+        choices = {{4, 1, win}, {2, 1, win}, {1, 1, win}};
+    } else if (n_t % 16 == 0) choices = {{4, 4, 1u << 17}, {4, 1, 1u << 17}, {2, 1, 1u << 17}, {1, 1, 1u << 17}};
     else if (n_t > 16 && n_t % 4 == 0) choices = {{2, 4, 1u << 15}, {4, 1, 1u << 15}, {2, 1, 1u << 15}, {1, 1, 1u << 15}};
     else if (n_t % 4 == 0) choices = {{4, 1, 1u << 15}, {2, 1, 1u << 15}, {1, 1, 1u << 15}};
     else choices = {{4, 1, 1u << 14}, {2, 1, 1u << 14}, {1, 1, 1u << 14}};
@@ -306,26 +316,13 @@ int build_tiles(bz_plan_s *p, uint32_t qpt, uint32_t vq, uint32_t window, hipStr
             }
         }
     }
-    // FP32 plans: NURBS tiles (a chain of dependent random loads per query,
-    // cold in steady state) spread evenly through the others instead of one
-    // run per window or class, so every stretch of the launch overlaps a few
-    // of them with the streaming Bezier tiles (measured faster for FP32
-    // storage, whose NURBS queries go through the bucket table, and no
-    // faster for 16-bit storage)
-    if (p->dtype == BZ_F32) {
-        std::vector<Tile> nb, rest;
-        for (const Tile &t : tiles) (t.ci.kind == 2 ? nb : rest).push_back(t);
-        if (!nb.empty() && !rest.empty()) {
-            tiles.clear();
-            const uint64_t R = rest.size(), N = nb.size();
-            size_t k = 0;
-            for (uint64_t i = 0; i < R; ++i) {  // NURBS tile k goes before other tile floor(k*R/N)
-                for (; k < N && k * R / N <= i; ++k) tiles.push_back(nb[k]);
-                tiles.push_back(rest[i]);
-            }
-            for (; k < N; ++k) tiles.push_back(nb[k]);
-        }
-    }
+    // FP32 plans: NURBS tiles, whose queries are chains of dependent loads and take
+    // about a sixth of a degree-15 tile's time, fill the launch's end (2^20 curves and
+    // 2^16 NURBS x 16: 131 us, 133 spread evenly among the others; with 2^16
+    // patches 139 and 152; 2^18 curves and 2^14 NURBS 30 and 40).  16-bit plans
+    // have them in their class's place.
+    if (p->dtype == BZ_F32)
+        std::stable_partition(tiles.begin(), tiles.end(), [](const Tile &t) { return t.ci.kind != 2; });
     const size_t n_main = tiles.size();
     for (int c : signed_cls) emit(c, 0, static_cast<uint64_t>(cls[c].count) * nt);
     if (p->tiles) BZ_CHECK_HIP(hipStreamSynchronize(s));
@@ -542,7 +539,7 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
             p->cus = static_cast<uint32_t>(std::max(1, cus));
         }
         if (!rc) {
-            const Layout l = default_layout(cls, n_t, p->cus);
+            const Layout l = default_layout(cls, method, n_t, p->cus);
             rc = build_tiles(p, l.qpt, l.vq, l.window, s);
         }
         if (!rc) rc = dmalloc(&p->ctrl_s, ctrl_elems * es);
