@@ -391,7 +391,7 @@ int bz_batch_eval_uv(bz_plan plan, const float *t, const float *v, float *out, b
  * first: neighbouring objects' parameter rows and points, which share cache
  * lines, are then read and written closer in time, and heavy and light
  * classes alternate through the launch; for FP32 storage, in either order,
- * the NURBS tiles are spread evenly among the others) x 2 lane mappings (one query per lane, or --
+ * the NURBS tiles come last) x 2 lane mappings (one query per lane, or --
  * when n_t is a multiple of 4 -- four consecutive parameters of one object per
  * lane) x 3 tile sizes (1, 2 or 4 sub-tiles of 256 lanes per tile) x 2
  * schedules (atomic tile counter, static round robin) x 4 grid sizes (8, 12,

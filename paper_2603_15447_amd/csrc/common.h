@@ -27,6 +27,15 @@ constexpr int kBlock = 256;
 // was 97, 138 and 299 us at 2^10, 2^17 and 2^20 segments' tiles, two 90, 132
 // and 299.
 constexpr int kChainQueries = 2;
+// Calls of 2^18 to 2^21 queries on a grid that the caches near the CUs hold are
+// over before wavefronts run short, and four queries share their launch better:
+// up to `small_seg` segments they keep four (2^20 queries, four against two: 1000
+// segments, grid 6.5 and 6.8 us, tiles 7.5 and 7.8, 16-bit 5.7 and 6.4, cubic tiles
+// 9.6 and 9.9; 8192: grid 9.6 and 8.7, tiles 7.7 and 8.5, cubic tiles 11.2 and 10.3; 2^17:
+// tiles 10.9 and 10.1, 16-bit 7.5 and 8.2).
+inline int chain_queries(uint32_t n_seg, uint32_t nq, uint32_t small_seg) {
+    return nq >= (1u << 18) && nq < (1u << 21) && n_seg <= small_seg ? 4 : kChainQueries;
+}
 
 // ------------------------------------------------------------------ host
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));

@@ -476,8 +476,9 @@ __global__ __launch_bounds__(kBlock) void k_to_seiler(const T *__restrict__ ctrl
 // ---------------------------------------------------------------- host
 // Which kernel: integral points of curves with n_t a multiple of 64 come from
 // scalar-loaded control points (staging them in LDS: 10.0 against 9.7 us for
-// 16384 cubics x 256), except in Seiler form, whose terms are then formed once
-// per curve (degree 7: 12.6 against 18.1 us).  Curves of fewer than
+// 16384 cubics x 256), except in Seiler form of degree 5 and up, whose terms are
+// then formed once per curve (65536 curves x 256, staged against scalar loads:
+// degree 3 37.5 and 29.6 us, 4 38.1 and 34.4, 5 37.3 and 42.0, 7 33.3 and 60.5).  Curves of fewer than
 // kMixedMinT queries are loaded per query: so many would be staged per workgroup
 // that it gets few of them (3,000,000 cubics x 1: 30 against 36 us).
 // Everything else is staged (40009 bf16 curves of degree 9 in 4D x 100: 17 us,
@@ -487,7 +488,7 @@ constexpr uint32_t kMixedMinT = 8;
 template <int F, bool RAT, typename T, int D, int DIM>
 void launch_curves_dd(CurveArgs a, hipStream_t s) {
     const uint32_t n_t = a.div_nt.d, flat = (a.nq + kBlock - 1) / kBlock;
-    if constexpr (!RAT && F != FORM_SEILER) {
+    if constexpr (!RAT && (F != FORM_SEILER || D <= 4)) {
         if (n_t % 64 == 0) {
             hipLaunchKernelGGL((k_curves<D, DIM, F, RAT, T, true>), dim3(flat), dim3(kBlock), 0, s, a);
             return;

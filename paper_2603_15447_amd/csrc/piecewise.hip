@@ -190,11 +190,13 @@ __global__ __launch_bounds__(kBlock) void k_piecewise_eval_tiled(const float *__
 template <int DIM>
 int launch_eval_tiled(const float *tiles, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                       hipStream_t s) {
-    constexpr int Q = kChainQueries;
-    const uint32_t per_block = kBlock * Q;
-    const uint32_t blocks = (nq + per_block - 1) / per_block;
-    hipLaunchKernelGGL((k_piecewise_eval_tiled<DIM, Q>), dim3(blocks), dim3(kBlock), 0, s, tiles, n_seg, T, nq, out,
-                       plane);
+    auto launch = [&](auto q) {
+        constexpr uint32_t per_block = kBlock * decltype(q)::value;
+        hipLaunchKernelGGL((k_piecewise_eval_tiled<DIM, decltype(q)::value>), dim3((nq + per_block - 1) / per_block),
+                           dim3(kBlock), 0, s, tiles, n_seg, T, nq, out, plane);
+    };
+    if (chain_queries(n_seg, nq, 1u << 14) == 4) launch(std::integral_constant<int, 4>{});
+    else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_eval_tiled");
     return BZ_OK;
 }
@@ -320,11 +322,13 @@ __global__ __launch_bounds__(kBlock) void k_piecewise_eval_tiled16(const uint16_
 template <int DIM, typename H>
 int launch_eval_tiled16(const uint16_t *tiles, uint32_t n_seg, const float *Tp, uint32_t nq, float *out, int64_t plane,
                         hipStream_t s) {
-    constexpr int Q = kChainQueries;
-    const uint32_t per_block = kBlock * Q;
-    const uint32_t blocks = (nq + per_block - 1) / per_block;
-    hipLaunchKernelGGL((k_piecewise_eval_tiled16<DIM, H, Q>), dim3(blocks), dim3(kBlock), 0, s, tiles, n_seg, Tp, nq,
-                       out, plane);
+    auto launch = [&](auto q) {
+        constexpr uint32_t per_block = kBlock * decltype(q)::value;
+        hipLaunchKernelGGL((k_piecewise_eval_tiled16<DIM, H, decltype(q)::value>),
+                           dim3((nq + per_block - 1) / per_block), dim3(kBlock), 0, s, tiles, n_seg, Tp, nq, out, plane);
+    };
+    if (chain_queries(n_seg, nq, UINT32_MAX) == 4) launch(std::integral_constant<int, 4>{});
+    else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_eval_tiled16");
     return BZ_OK;
 }
@@ -340,12 +344,12 @@ int eval_tiled16_dim(int dim, const uint16_t *tiles, uint32_t ns, const float *T
     }
 }
 
-// Queries per thread; BZ_PIECEWISE_QPT (1, 2, 4 or 8) overrides kChainQueries.
+// BZ_PIECEWISE_QPT (1, 2, 4 or 8) overrides the queries per thread; 0: not set.
 int piecewise_qpt() {
     static const int q = [] {
         const char *e = getenv("BZ_PIECEWISE_QPT");
-        const int v = e ? atoi(e) : kChainQueries;
-        return (v == 1 || v == 2 || v == 4 || v == 8) ? v : kChainQueries;
+        const int v = e ? atoi(e) : 0;
+        return (v == 1 || v == 2 || v == 4 || v == 8) ? v : 0;
     }();
     return q;
 }
@@ -363,7 +367,8 @@ int launch_eval_q(const float *grid, uint32_t n_seg, const float *T, uint32_t nq
 template <int DIM>
 int launch_eval(const float *grid, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                 hipStream_t s) {
-    switch (piecewise_qpt()) {
+    const int qpt = piecewise_qpt();
+    switch (qpt ? qpt : chain_queries(n_seg, nq, 1u << 12)) {
         case 1: return launch_eval_q<DIM, 1>(grid, n_seg, T, nq, out, plane, s);
         case 2: return launch_eval_q<DIM, 2>(grid, n_seg, T, nq, out, plane, s);
         case 8: return launch_eval_q<DIM, 8>(grid, n_seg, T, nq, out, plane, s);

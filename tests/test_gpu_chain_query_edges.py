@@ -49,3 +49,20 @@ def test_query_counts(orc, dim):
             f(t[:n], flat[:dim * n].view(dim, n))
             assert torch.equal(flat[:dim * n].view(dim, n), full[:, :n]), (name, n)
             assert bool((flat[dim * n:] == -7.0).all()), (name, n)
+
+
+@pytest.mark.parametrize("n_q", [(1 << 18) - 1, 1 << 18, (1 << 19) + 5, (1 << 21) - 1, 1 << 21])
+@pytest.mark.parametrize("n_seg", [N_SEG, 1 << 13, 1 << 15])
+def test_queries_per_thread(n_q, n_seg):
+    """On both sides of the rule for four queries per thread: the results of
+    calls far below it, bit for bit."""
+    chain, T = bz_synth.chain_walk(n_seg=n_seg, dim=3, n_q=n_q, seed=n_seg)
+    cubic, _ = bz_synth.cubic_chain_walk(n_seg=n_seg, dim=3, n_q=1, seed=n_seg)
+    grid, grid3 = bz.encode_piecewise(to_dev(chain)), bz.encode_piecewise_cubic(to_dev(cubic))
+    tiles, half, tiles3 = bz.tile_piecewise(grid), bz.tile_piecewise16(grid, torch.float16), bz.tile_piecewise_cubic(grid3)
+    t = to_dev(T)
+    for f in (lambda x: bz.eval_piecewise(grid, x), lambda x: bz.eval_piecewise_tiled(tiles, n_seg, 3, x),
+              lambda x: bz.eval_piecewise_tiled16(half, n_seg, 3, x),
+              lambda x: bz.eval_piecewise_cubic_tiled(tiles3, n_seg, 3, x)):
+        parts = [f(x) for x in torch.split(t, 100000)]
+        assert torch.equal(f(t), torch.cat(parts, dim=1))
