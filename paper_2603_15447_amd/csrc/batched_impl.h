@@ -410,6 +410,61 @@ __device__ __forceinline__ void run_curve_tile4(const BatchArgs &a, const Tile &
     }
 }
 
+// The shares (u-a) / (b-a) and (b-u) / (b-a) of a knot interval at its parameter
+// u, a < b, at any size of either: the interval is scaled by a power of two first,
+// and the larger share is what the smaller leaves of 1, so that an infinite end
+// takes all.
+__device__ __forceinline__ void knot_shares(float a, float b, float u, float &x, float &y) {
+    const float w = b - a, sc = w < 0x1p-60f ? 0x1p60f : w <= 0x1p100f ? 1.0f : 0.25f;
+    const float l = u * sc - a * sc, r = b * sc - u * sc;
+    const bool left = l <= r;
+    const float m = (left ? l : r) / (l + r);
+    x = left ? m : 1.0f - m;
+    y = left ? 1.0f - m : m;
+}
+
+// N[0..3]: the cubic basis functions that don't vanish on the span [K[2], K[3])
+// of the knots K, at its parameter u.
+__device__ __forceinline__ void nurbs_basis(const float (&K)[6], float u, float (&N)[4]) {
+    if (__builtin_expect(K[5] - K[0] <= 0x1p60f && K[3] - K[2] >= 0x1p-60f, 1)) {
+        // each divisor a sum of knot distances that covers the span
+        const float l1 = u - K[2], l2 = u - K[1], l3 = u - K[0], r1 = K[3] - u, r2 = K[4] - u, r3 = K[5] - u;
+        float p = 1.0f / (r1 + l1);
+        N[0] = r1 * p;
+        N[1] = l1 * p;
+        p = N[0] / (r1 + l2);
+        const float p2 = N[1] / (r2 + l1);
+        N[0] = r1 * p;
+        N[1] = __builtin_fmaf(r2, p2, l2 * p);
+        N[2] = l1 * p2;
+        p = N[0] / (r1 + l3);
+        const float p3 = N[1] / (r2 + l2), p4 = N[2] / (r3 + l1);
+        N[0] = r1 * p;
+        N[1] = __builtin_fmaf(r2, p3, l3 * p);
+        N[2] = __builtin_fmaf(r3, p4, l2 * p3);
+        N[3] = l1 * p4;
+        return;
+    }
+    // knots whose distances, or a distance's reciprocal, may leave FP32's range,
+    // some large and some small at once: every interval on its own
+    float x, y, x2, y2, x3, y3;
+    knot_shares(K[2], K[3], u, x, y);
+    N[0] = y;
+    N[1] = x;
+    knot_shares(K[1], K[3], u, x, y);
+    knot_shares(K[2], K[4], u, x2, y2);
+    N[2] = x2 * N[1];
+    N[1] = __builtin_fmaf(y2, N[1], x * N[0]);
+    N[0] = y * N[0];
+    knot_shares(K[0], K[3], u, x, y);
+    knot_shares(K[1], K[4], u, x2, y2);
+    knot_shares(K[2], K[5], u, x3, y3);
+    N[3] = x3 * N[2];
+    N[2] = __builtin_fmaf(y3, N[2], x2 * N[1]);
+    N[1] = __builtin_fmaf(y2, N[1], x * N[0]);
+    N[0] = y * N[0];
+}
+
 // NURBS queries, staged across the sub-tiles so that the dependent loads of
 // one stage (header and object index; parameter; table entries; knots; control
 // points) overlap over all of a lane's queries: clamp u to the NURBS's range,
@@ -491,27 +546,8 @@ __device__ __forceinline__ void run_nurbs_tile(const BatchArgs &a, const Tile &t
 #pragma unroll
     for (int s = 0; s < Q; ++s) {
         if (!ok[s]) continue;
-        // N[0..3]: basis functions span-3 .. span, each divisor a sum of knot
-        // distances that covers the non-empty span
-        // (only ratios count: knots of extreme size or distance are scaled first)
-        const float sc = K[s][5] - K[s][0] > 0x1p60f ? 0x1p-60f : K[s][3] - K[s][2] < 0x1p-60f ? 0x1p60f : 1.0f;
-        const float l1 = (u[s] - K[s][2]) * sc, l2 = (u[s] - K[s][1]) * sc, l3 = (u[s] - K[s][0]) * sc;
-        const float r1 = (K[s][3] - u[s]) * sc, r2 = (K[s][4] - u[s]) * sc, r3 = (K[s][5] - u[s]) * sc;
         float N[4];
-        float p = 1.0f / (r1 + l1);
-        N[0] = r1 * p;
-        N[1] = l1 * p;
-        p = N[0] / (r1 + l2);
-        const float p2 = N[1] / (r2 + l1);
-        N[0] = r1 * p;
-        N[1] = __builtin_fmaf(r2, p2, l2 * p);
-        N[2] = l1 * p2;
-        p = N[0] / (r1 + l3);
-        const float p3 = N[1] / (r2 + l2), p4 = N[2] / (r3 + l1);
-        N[0] = r1 * p;
-        N[1] = __builtin_fmaf(r2, p3, l3 * p);
-        N[2] = __builtin_fmaf(r3, p4, l2 * p3);
-        N[3] = l1 * p4;
+        nurbs_basis(K[s], u[s], N);
         float den = 0.0f, acc[DIM] = {};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
