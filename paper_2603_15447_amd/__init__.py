@@ -137,12 +137,15 @@ def _ptr(x):
 
 
 # The current device's current stream as a handle: torch.cuda.current_stream()
-# builds a Stream object for it, 2.7 us of a small call's 9.6.
-_current_device = torch._C._cuda_getDevice
-_current_stream = torch._C._cuda_getCurrentRawStream
+# builds a Stream object for it, 2.7 us of a small call's 9.6.  (A torch built
+# without a GPU has neither function; calls then fail as torch.cuda does.)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
+    if _current_device is None or _current_stream is None:
+        return torch.cuda.current_stream().cuda_stream
     return _current_stream(_current_device())
 
 
