@@ -395,15 +395,19 @@ int bz_batch_eval_uv(bz_plan plan, const float *t, const float *v, float *out, b
  * when n_t is a multiple of 4 -- four consecutive parameters of one object per
  * lane) x 3 tile sizes (1, 2 or 4 sub-tiles of 256 lanes per tile) x 2
  * schedules (atomic tile counter, static round robin) x 4 grid sizes (8, 12,
- * 16, 64 workgroups per CU) and keeps the fastest in the plan.
+ * 16, 64 workgroups per CU) and keeps the fastest of these and of what the plan
+ * launched before in the plan.
  * (The timing launches of a plan with patches read the patches' v from t.)  Without
  * autotuning a plan launches 64 workgroups per CU with the static schedule and
  * tiles chosen by n_t and the batch's size: 4 sub-tiles, four parameters per
- * lane and windows of 2^17 objects when n_t is a multiple of 16, smaller windows
- * and one parameter per lane for short or odd rows, smaller tiles where a batch
- * is too small to give every CU one.  No launch has more workgroups than tiles.
- * Synchronises the stream.  best6 (nullable, host, 6 values): workgroups, sub-tiles per tile, microseconds per launch, schedule
- * (1 dynamic, 0 static), queries per lane, window (0: class-major).
+ * lane and windows of 2^17 objects when n_t is a multiple of 16 (de Casteljau: 2
+ * sub-tiles, and one parameter per lane in batches of fewer than 16 tiles of 2048
+ * queries per CU), smaller windows and one parameter per lane for short or odd
+ * rows, smaller tiles where a batch is too small to give every CU one.  No launch
+ * has more workgroups than tiles.
+ * Synchronises the stream.  best6 (nullable, host, 6 values): workgroups,
+ * sub-tiles per tile, microseconds per launch, schedule (1 dynamic, 0 static),
+ * queries per lane, window (0: class-major).
  */
 int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream stream, int64_t *best6);
 /*

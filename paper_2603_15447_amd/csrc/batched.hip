@@ -641,7 +641,7 @@ int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream s
         BZ_CHECK_HIP(hipEventCreate(&e0));
         BZ_CHECK_HIP(hipEventCreate(&e1));
         const uint32_t cus = plan->cus;
-        float best = 1e30f;
+        float best = 0.0f;
         uint32_t best_wg = plan->workgroups, best_q = plan->qpt, best_vq = plan->vq, best_win = plan->window;
         int best_dyn = plan->dynamic;
         const uint32_t qpts[] = {1, 2, 4};
@@ -675,10 +675,14 @@ int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream s
             *ms_out = ms;
             return r0;
         };
-        int rc = BZ_OK;
+        // what the plan launches so far first: its layout (the default one of short
+        // or odd rows, or a configured one) need not be among those searched (the
+        // second timing counts: the first may find the GPU idle)
+        int rc = time_cfg(plan->workgroups, plan->dynamic, plan->vq, &best);
+        if (!rc) rc = time_cfg(plan->workgroups, plan->dynamic, plan->vq, &best);
         for (const Layout &L : layouts) {
-            rc = build_tiles(plan, L.qpt, L.vq, L.window, s);
             if (rc) break;
+            rc = build_tiles(plan, L.qpt, L.vq, L.window, s);
             for (int dyn = 1; dyn >= 0 && !rc; --dyn)
                 for (uint32_t f : wg_per_cu) {
                     float ms = 0;
@@ -693,7 +697,6 @@ int bz_batch_plan_autotune(bz_plan plan, const float *t, float *out, bz_stream s
                         best_win = L.window;
                     }
                 }
-            if (rc) break;
         }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
