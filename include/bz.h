@@ -125,8 +125,10 @@ int bz_eval_rational(const void *ctrl, const void *w, int dtype, int64_t n_curve
  *        (x_k + x_{k+1})/2 = M_k (the diagonal texels of segment k average
  *        to its middle control point).  The free texels are formed by an
  *        FP64 alternating prefix sum and rounded once to FP32.
- * Allocates nothing: block sums pass through grid itself, which must not
- * overlap chain.
+ * Allocates nothing: block sums pass through grid itself.  grid must not overlap
+ * chain, except that it may be chain (whose buffer then ends with the one row that
+ * grid is longer): encoded in place, a chain uses a small stream-ordered device
+ * workspace (hipMallocAsync) instead.
  */
 int bz_encode_piecewise(const float *chain, int64_t n_seg, int dim, float *grid, bz_stream stream);
 
@@ -135,9 +137,11 @@ int bz_encode_piecewise(const float *chain, int64_t n_seg, int dim, float *grid,
  * must not allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc).  Same arguments, same results bit
  * for bit; it allocates nothing and keeps no state, so calls may overlap on
- * different streams or threads.  Limit: n_seg <= floor(2^18/dim)*2048 - 1
- * (536870911, 268435455, 178956287, 134217727 for dim 1..4); larger n_seg
- * returns BZ_ERR_SHAPE.
+ * different streams or threads -- except calls in place (grid == chain), which
+ * keep their block sums in a fixed 2 MiB device array of the library (a copy per
+ * device): those on one device must be serialised by the caller.  Limit: n_seg <=
+ * floor(2^18/dim)*2048 - 1 (536870911, 268435455, 178956287, 134217727 for dim
+ * 1..4); larger n_seg returns BZ_ERR_SHAPE.
  */
 int bz_encode_piecewise_noalloc(const float *chain, int64_t n_seg, int dim, float *grid, bz_stream stream);
 

@@ -123,6 +123,36 @@ __device__ __forceinline__ double wave_sum64(double v) {
 // that block reads it in the last pass, before it writes the column, so the
 // encoder needs no workspace.  (hipMallocAsync and hipFreeAsync of a small one
 // cost 20 us of host time per call, more than all passes at 2^18 segments.)
+struct EncInGrid {
+    static constexpr bool kInPlace = false;
+    using In = const float *__restrict__;
+    using Out = float *__restrict__;
+};
+
+// A quadratic chain encoded in place (grid == chain) has no such column, and its
+// own first column is gone when the last blocks come to start from M_0: the sums
+// wait in a workspace, the block's own behind each other, and M_0 behind them.
+struct EncInPlace {
+    static constexpr bool kInPlace = true;
+    using In = const float *;
+    using Out = float *;
+    float *ws;  // nullptr: g_enc_scratch
+    int64_t nb;
+};
+
+// Workspace of chains encoded in place without an allocation: as many doubles as
+// the longest of them takes.
+constexpr int64_t kEncScratchDoubles = int64_t(1) << 18;
+__device__ double g_enc_scratch[kEncScratchDoubles + kMaxDim];
+
+// Place of block b's sum (b = nb in place: of M_0).
+template <int NCH>
+__device__ __forceinline__ float *enc_place(EncInGrid, float *grid, int64_t cols, int64_t b) { return grid + b * cols * 2 * NCH; }
+template <int NCH>
+__device__ __forceinline__ float *enc_place(EncInPlace at, float *, int64_t, int64_t b) {
+    return (at.ws ? at.ws : reinterpret_cast<float *>(g_enc_scratch)) + b * 2 * NCH;
+}
+
 __device__ __forceinline__ void enc_put(float *p, int ch, double v) {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
     p[2 * ch] = __uint_as_float(static_cast<uint32_t>(u));
@@ -132,9 +162,9 @@ __device__ __forceinline__ double enc_get(const float *p, int ch) {
     return __builtin_bit_cast(double, __float_as_uint(p[2 * ch]) | static_cast<uint64_t>(__float_as_uint(p[2 * ch + 1])) << 32);
 }
 
-template <int DIM, int ROWS, int NT>
-__global__ __launch_bounds__(NT) void k_enc_partials(const float *__restrict__ chain, int64_t n_seg,
-                                                     float *__restrict__ grid) {
+template <int DIM, int ROWS, int NT, typename S>
+__global__ __launch_bounds__(NT) void k_enc_partials(const float *__restrict__ chain, int64_t n_seg, float *__restrict__ grid,
+                                                     S sums) {
     using G = EncGeom<DIM, ROWS, NT>;
     __shared__ float lds[G::LDS];
     __shared__ double wsum[G::WAVES][G::NCH];
@@ -154,7 +184,10 @@ __global__ __launch_bounds__(NT) void k_enc_partials(const float *__restrict__ c
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < G::WAVES; ++w) s += wsum[w][threadIdx.x];
-        enc_put(grid + col0 * 2 * G::NCH, threadIdx.x, s);
+        enc_put(enc_place<G::NCH>(sums, grid, G::COLS, blockIdx.x), threadIdx.x, s);
+        if constexpr (S::kInPlace) {  // (a quadratic chain)
+            if (blockIdx.x == 0) enc_put(enc_place<G::NCH>(sums, grid, 0, sums.nb), threadIdx.x, chain[DIM + threadIdx.x]);
+        }
     }
 }
 
@@ -162,15 +195,15 @@ __global__ __launch_bounds__(NT) void k_enc_partials(const float *__restrict__ c
 // blocks of the chain (`cols` columns each) at a time.
 constexpr int kScanThreads = 1024;
 
-template <int NCH>
-__global__ __launch_bounds__(kScanThreads) void k_enc_offsets(int64_t nb, int cols, float *__restrict__ grid) {
+template <int NCH, typename S>
+__global__ __launch_bounds__(kScanThreads) void k_enc_offsets(int64_t nb, int cols, float *__restrict__ grid, S sums) {
     constexpr int WAVES = kScanThreads / 64;
     __shared__ double wsum[WAVES][NCH];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double carry[NCH] = {};
     for (int64_t b0 = 0; b0 < nb; b0 += kScanThreads) {
         const int64_t b = b0 + threadIdx.x;
-        float *__restrict__ p = grid + b * cols * 2 * NCH;
+        float *__restrict__ p = enc_place<NCH>(sums, grid, cols, b);
         double v[NCH], incl[NCH];
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) incl[ch] = v[ch] = b < nb ? enc_get(p, ch) : 0.0;
@@ -202,10 +235,11 @@ __global__ __launch_bounds__(kScanThreads) void k_enc_offsets(int64_t nb, int co
 // Writes the columns of a block: the endpoint in row k mod 2, the free texel
 // in the other row.  Output [N+1][layers][2][DIM] (layers = ROWS - 1).
 // DIRECT: the block adds up the chain before it itself (chains of a few
-// blocks, in one launch); otherwise the grid holds the sum before the block.
-template <int DIM, int ROWS, int NT, bool DIRECT>
-__global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chain, int64_t n_seg,
-                                                  float *__restrict__ grid) {
+// blocks, in one launch); otherwise the sum before the block waits for it.
+// (In place a block stages its columns before it writes the same, and reads no
+// others.)
+template <int DIM, int ROWS, int NT, bool DIRECT, typename S>
+__global__ __launch_bounds__(NT) void k_enc_write(typename S::In chain, int64_t n_seg, typename S::Out grid, S sums) {
     using G = EncGeom<DIM, ROWS, NT>;
     constexpr int NCH = G::NCH;
     __shared__ float lds[G::LDS];
@@ -216,7 +250,7 @@ __global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chai
     double pre[NCH] = {};
     if constexpr (!DIRECT) {
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) pre[ch] = enc_get(grid + col0 * 2 * NCH, ch);
+        for (int ch = 0; ch < NCH; ++ch) pre[ch] = enc_get(enc_place<NCH>(sums, grid, G::COLS, blockIdx.x), ch);
     } else {
         const int n = static_cast<int>(col0);  // a multiple of NT: column parity is the thread's
 #pragma unroll 4
@@ -257,9 +291,14 @@ __global__ __launch_bounds__(NT) void k_enc_write(const float *__restrict__ chai
     float *run = lds + threadIdx.x * (G::OUT | 1);
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
-        const float *__restrict__ c0 = chain;
-        auto row = [&](int j) { return c0[j]; };
-        double y = 0.5 * enc_twice_mid<DIM, ROWS>(row, ch);  // M_0
+        double y;  // M_0
+        if constexpr (S::kInPlace) {
+            y = enc_get(enc_place<NCH>(sums, grid, 0, sums.nb), ch);
+        } else {
+            typename S::In c0 = chain;
+            auto row = [&](int j) { return c0[j]; };
+            y = 0.5 * enc_twice_mid<DIM, ROWS>(row, ch);
+        }
         if constexpr (!DIRECT) {
             y += pre[ch];
         } else {
@@ -309,40 +348,48 @@ template <int ROWS>
 constexpr int kEncLongThreads = ROWS == 2 ? 512 : 256;
 constexpr int64_t kEncSmallCols = int64_t(1) << 18, kEncDirectCols = int64_t(1) << 15;
 
-template <int DIM, int ROWS, int NT>
-void launch_encode_blocks(const float *chain, int64_t n_seg, float *grid, hipStream_t s) {
+template <int DIM, int ROWS, int NT, typename S>
+void launch_encode_blocks(const float *chain, int64_t n_seg, float *grid, S sums, hipStream_t s) {
     constexpr int COLS = EncGeom<DIM, ROWS, NT>::COLS, NCH = EncGeom<DIM, ROWS, NT>::NCH;
     const int64_t nb = (n_seg + COLS) / COLS;
     const dim3 blocks(static_cast<uint32_t>(nb));
-    hipLaunchKernelGGL((k_enc_partials<DIM, ROWS, NT>), blocks, dim3(NT), 0, s, chain, n_seg, grid);
-    hipLaunchKernelGGL((k_enc_offsets<NCH>), dim3(1), dim3(kScanThreads), 0, s, nb, COLS, grid);
-    hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NT, false>), blocks, dim3(NT), 0, s, chain, n_seg, grid);
+    hipLaunchKernelGGL((k_enc_partials<DIM, ROWS, NT, S>), blocks, dim3(NT), 0, s, chain, n_seg, grid, sums);
+    hipLaunchKernelGGL((k_enc_offsets<NCH, S>), dim3(1), dim3(kScanThreads), 0, s, nb, COLS, grid, sums);
+    hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NT, false, S>), blocks, dim3(NT), 0, s, chain, n_seg, grid, sums);
 }
 
 template <int DIM, int ROWS>
-void launch_encode(const float *chain, int64_t n_seg, float *grid, hipStream_t s) {
+void launch_encode(const float *chain, int64_t n_seg, float *grid, EncInGrid sums, hipStream_t s) {
     constexpr int NL = kEncLongThreads<ROWS>, COLS = EncGeom<DIM, ROWS, NL>::COLS;
     if (n_seg + 1 <= kEncDirectCols)
-        hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NL, true>), dim3(static_cast<uint32_t>((n_seg + COLS) / COLS)),
-                           dim3(NL), 0, s, chain, n_seg, grid);
+        hipLaunchKernelGGL((k_enc_write<DIM, ROWS, NL, true, EncInGrid>), dim3(static_cast<uint32_t>((n_seg + COLS) / COLS)),
+                           dim3(NL), 0, s, chain, n_seg, grid, sums);
     else if (n_seg + 1 <= kEncSmallCols)
-        launch_encode_blocks<DIM, ROWS, kEncShortThreads>(chain, n_seg, grid, s);
+        launch_encode_blocks<DIM, ROWS, kEncShortThreads>(chain, n_seg, grid, sums, s);
     else
-        launch_encode_blocks<DIM, ROWS, NL>(chain, n_seg, grid, s);
+        launch_encode_blocks<DIM, ROWS, NL>(chain, n_seg, grid, sums, s);
 }
 
-template <int ROWS>
-void launch_encode_dim(int dim, const float *chain, int64_t n_seg, float *grid, hipStream_t s) {
+// In place: long blocks whatever the size, as the workspace is counted in them.
+template <int DIM, int ROWS>
+void launch_encode(const float *chain, int64_t n_seg, float *grid, EncInPlace sums, hipStream_t s) {
+    launch_encode_blocks<DIM, ROWS, kEncLongThreads<ROWS>>(chain, n_seg, grid, sums, s);
+}
+
+template <int ROWS, typename S>
+void launch_encode_dim(int dim, const float *chain, int64_t n_seg, float *grid, S sums, hipStream_t s) {
     switch (dim) {
-        case 1: launch_encode<1, ROWS>(chain, n_seg, grid, s); break;
-        case 2: launch_encode<2, ROWS>(chain, n_seg, grid, s); break;
-        case 3: launch_encode<3, ROWS>(chain, n_seg, grid, s); break;
-        default: launch_encode<4, ROWS>(chain, n_seg, grid, s); break;
+        case 1: launch_encode<1, ROWS>(chain, n_seg, grid, sums, s); break;
+        case 2: launch_encode<2, ROWS>(chain, n_seg, grid, sums, s); break;
+        case 3: launch_encode<3, ROWS>(chain, n_seg, grid, sums, s); break;
+        default: launch_encode<4, ROWS>(chain, n_seg, grid, sums, s); break;
     }
 }
 
-// Longest chain bz_encode_piecewise_noalloc takes, part of its interface.
-int64_t noalloc_max_seg(int dim) { return (int64_t(1) << 18) / dim * 2048 - 1; }
+// Longest chain bz_encode_piecewise_noalloc takes, part of its interface: its
+// blocks' sums fit g_enc_scratch.
+constexpr int64_t kEncLongCols = EncGeom<1, 2, kEncLongThreads<2>>::COLS;
+int64_t noalloc_max_seg(int dim) { return kEncScratchDoubles / dim * kEncLongCols - 1; }
 
 }  // namespace
 }  // namespace bzi
@@ -351,7 +398,9 @@ using namespace bzi;
 
 extern "C" {
 
-static int encode_chain(const char *fn, const float *chain, int64_t n_seg, int dim, int cubic, float *grid,
+// alloc: whether a chain encoded in place may take a workspace from the stream's
+// memory; else it takes the library's.
+static int encode_chain(const char *fn, const float *chain, int64_t n_seg, int dim, int cubic, bool alloc, float *grid,
                         bz_stream stream) {
     if (dim < 1 || dim > kMaxDim) return fail(BZ_ERR_SHAPE, "%s: dim %d", fn, dim);
     if (n_seg < 0 || n_seg > (int64_t(1) << 40)) return fail(BZ_ERR_SHAPE, "%s: n_seg %lld", fn, (long long)n_seg);
@@ -359,8 +408,22 @@ static int encode_chain(const char *fn, const float *chain, int64_t n_seg, int d
     if (!chain || !grid) return fail(BZ_ERR_NULL, "%s: chain and grid are required", fn);
     if (!aligned(chain, 4) || !aligned(grid, 4)) return fail(BZ_ERR_ALIGN, "%s: misaligned", fn);
     const hipStream_t s = as_stream(stream);
-    if (cubic) launch_encode_dim<3>(dim, chain, n_seg, grid, s);
-    else launch_encode_dim<2>(dim, chain, n_seg, grid, s);
+    if (cubic) {
+        launch_encode_dim<3>(dim, chain, n_seg, grid, EncInGrid{}, s);
+    } else if (grid != chain) {
+        launch_encode_dim<2>(dim, chain, n_seg, grid, EncInGrid{}, s);
+    } else {
+        EncInPlace at{nullptr, (n_seg + kEncLongCols) / kEncLongCols};
+        if (alloc) {
+            const hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&at.ws), sizeof(double) * (at.nb + 1) * dim, s);
+            if (e == hipErrorOutOfMemory) return fail(BZ_ERR_NOMEM, "%s: workspace", fn);
+            BZ_CHECK_HIP(e);
+        }
+        launch_encode_dim<2>(dim, chain, n_seg, grid, at, s);
+        const hipError_t le = hipGetLastError();
+        if (alloc) BZ_CHECK_HIP(hipFreeAsync(at.ws, s));
+        if (le != hipSuccess) return hip_fail(le, fn);
+    }
     BZ_CHECK_LAUNCH(fn);
     return BZ_OK;
 }
@@ -372,18 +435,18 @@ int bz_encode_piecewise_noalloc(const float *chain, int64_t n_seg, int dim, floa
         if (n_seg < 0 || n_seg > noalloc_max_seg(dim))
             return fail(BZ_ERR_SHAPE, "%s: n_seg %lld outside 0..%lld, the workspace limit for dim %d", fn,
                         (long long)n_seg, (long long)noalloc_max_seg(dim), dim);
-        return encode_chain(fn, chain, n_seg, dim, 0, grid, stream);
+        return encode_chain(fn, chain, n_seg, dim, 0, false, grid, stream);
     });
 }
 
 int bz_encode_piecewise(const float *chain, int64_t n_seg, int dim, float *grid, bz_stream stream) {
     return guarded("bz_encode_piecewise",
-                   [&]() -> int { return encode_chain("bz_encode_piecewise", chain, n_seg, dim, 0, grid, stream); });
+                   [&]() -> int { return encode_chain("bz_encode_piecewise", chain, n_seg, dim, 0, true, grid, stream); });
 }
 
 int bz_encode_piecewise_cubic(const float *chain, int64_t n_seg, int dim, float *grid, bz_stream stream) {
     return guarded("bz_encode_piecewise_cubic", [&]() -> int {
-        return encode_chain("bz_encode_piecewise_cubic", chain, n_seg, dim, 1, grid, stream);
+        return encode_chain("bz_encode_piecewise_cubic", chain, n_seg, dim, 1, true, grid, stream);
     });
 }
 
