@@ -59,6 +59,9 @@ int run_chunks(int form, bool rat, int dt, const void *ctrl, const void *w, int6
     const int64_t nq = n_curves * n_t;
     const int64_t per = std::max<int64_t>(1, kMaxLaunchQueries / n_t);
     const int es = dtype_size(dt);
+    const uintptr_t tb = reinterpret_cast<uintptr_t>(t), ob = reinterpret_cast<uintptr_t>(out);
+    const bool t_in_out = t_mode == BZ_T_PER_OBJECT && tb < ob + 4 * static_cast<uintptr_t>(dim) * nq &&
+                          ob < tb + 4 * static_cast<uintptr_t>(nq);
     for (int64_t c0 = 0; c0 < n_curves; c0 += per) {
         const int64_t nc = std::min(per, n_curves - c0);
         CurveArgs a;
@@ -74,6 +77,7 @@ int run_chunks(int form, bool rat, int dt, const void *ctrl, const void *w, int6
         a.per_object = t_mode == BZ_T_PER_OBJECT;
         a.kappa = kappa;
         a.n_fixed = n_fixed;
+        a.t_in_out = t_in_out;
         int rc;
         if (form == FORM_SEILER_PRE) rc = launch_curves_t<FORM_SEILER_PRE, false, float>(degree, dim, a, s);
         else if (dt == BZ_F32) rc = dispatch_form<float>(form, rat, degree, dim, a, s);

@@ -232,6 +232,7 @@ struct CurveArgs {
     int per_object;        // t[n][n_t] vs t[n_t]
     float kappa;           // rational conditioning threshold (<= 0: off)
     uint32_t *n_fixed;     // nullable device counter
+    bool t_in_out;         // the points overwrite the parameters (t a plane of out, say)
     // k_curves_mixed: queries per workgroup, curves it may touch, and whether the
     // planes lie alike to the 64-byte lines
     int chunk, slots, same;
@@ -480,7 +481,9 @@ __global__ __launch_bounds__(kBlock) void k_to_seiler(const T *__restrict__ ctrl
 // then formed once per curve (65536 curves x 256, staged against scalar loads:
 // degree 3 37.5 and 29.6 us, 4 38.1 and 34.4, 5 37.3 and 42.0, 7 33.3 and 60.5).  Curves of fewer than
 // kMixedMinT queries are loaded per query: so many would be staged per workgroup
-// that it gets few of them (3,000,000 cubics x 1: 30 against 36 us).
+// that it gets few of them (3,000,000 cubics x 1: 30 against 36 us).  So are
+// parameters that the points overwrite: a thread then reads no parameter but its
+// own query's, where a staged workgroup evaluates up to 31 of the one before.
 // Everything else is staged (40009 bf16 curves of degree 9 in 4D x 100: 17 us,
 // 20 per query).
 constexpr uint32_t kMixedMinT = 8;
@@ -494,7 +497,7 @@ void launch_curves_dd(CurveArgs a, hipStream_t s) {
             return;
         }
     }
-    if (n_t < kMixedMinT) {
+    if (n_t < kMixedMinT || a.t_in_out) {
         hipLaunchKernelGGL((k_curves<D, DIM, F, RAT, T, false>), dim3(flat), dim3(kBlock), 0, s, a);
         return;
     }
