@@ -475,18 +475,37 @@ __global__ __launch_bounds__(kBlock) void k_to_seiler(const T *__restrict__ ctrl
 }
 
 // ---------------------------------------------------------------- host
-// Which kernel: integral points of curves with n_t a multiple of 64 come from
+// Which kernel.  Integral points of curves with n_t a multiple of 64 come from
 // scalar-loaded control points (staging them in LDS: 10.0 against 9.7 us for
 // 16384 cubics x 256), except in Seiler form of degree 5 and up, whose terms are
 // then formed once per curve (65536 curves x 256, staged against scalar loads:
-// degree 3 37.5 and 29.6 us, 4 38.1 and 34.4, 5 37.3 and 42.0, 7 33.3 and 60.5).  Curves of fewer than
-// kMixedMinT queries are loaded per query: so many would be staged per workgroup
-// that it gets few of them (3,000,000 cubics x 1: 30 against 36 us).  So are
-// parameters that the points overwrite: a thread then reads no parameter but its
-// own query's, where a staged workgroup evaluates up to 31 of the one before.
-// Everything else is staged (40009 bf16 curves of degree 9 in 4D x 100: 17 us,
-// 20 per query).
+// degree 3 37.5 and 29.6 us, 4 38.1 and 34.4, 5 37.3 and 42.0, 7 33.3 and 60.5).
+// Parameters that the points overwrite are read by one thread per query: a thread
+// then reads no parameter but its own query's, where a staged workgroup evaluates
+// up to 31 of the one before.
+// Otherwise one thread per query is the faster in small calls, whose time is the
+// chain of a workgroup's stages, and staging in large ones, whose time is the
+// loads and conversions of a curve's coefficients for each of its queries.  The
+// line lies the lower, the more staging saves: terms formed once (Seiler), high
+// degrees, and curves of 64, 128, ... queries, few of them per workgroup; and
+// higher for curves of under 12 queries, many of them per workgroup.  Queries
+// from which on calls are staged, as log2, by degree (up to 5, 10, 15), from
+// 7,000 random calls on rotating buffers: so chosen they take 1.1 % more time
+// than with the better kernel each, all staged 16 % more, all with one thread per
+// query 7 % (118 rational curves of degree 5 in 3D, BF16, x 45: 2.3 us with a
+// thread per query, 3.3 staged; 9754 of degree 15 in 4D, FP16, Seiler form x 36:
+// 10.7 and 5.6; 100,003 rational quintics x 50: 22.0 either way).
+// Curves of fewer than kMixedMinT queries are never staged (3,000,000 cubics x 1:
+// 30 us with a thread per query, 36 staged).
 constexpr uint32_t kMixedMinT = 8;
+
+template <int F, bool RAT, int D>
+constexpr int staged_log2() {
+    constexpr int g = D <= 5 ? 0 : D <= 10 ? 1 : 2;
+    constexpr int dc[2][3] = {{23, 23, 22}, {23, 22, 21}}, bern[2][3] = {{21, 20, 20}, {23, 22, 22}};
+    constexpr int seiler[2][3] = {{21, 19, 17}, {22, 19, 18}}, terms[3] = {21, 20, 18};
+    return F == FORM_DC ? dc[RAT][g] : F == FORM_BERN ? bern[RAT][g] : F == FORM_SEILER ? seiler[RAT][g] : terms[g];
+}
 
 template <int F, bool RAT, typename T, int D, int DIM>
 void launch_curves_dd(CurveArgs a, hipStream_t s) {
@@ -497,7 +516,8 @@ void launch_curves_dd(CurveArgs a, hipStream_t s) {
             return;
         }
     }
-    if (n_t < kMixedMinT || a.t_in_out) {
+    const int from = staged_log2<F, RAT, D>() - (n_t % 64 == 0 ? (F == FORM_SEILER ? 1 : 2) : 0) + (n_t < 12 ? 2 : 0);
+    if (n_t < kMixedMinT || a.t_in_out || a.nq < 1u << from) {
         hipLaunchKernelGGL((k_curves<D, DIM, F, RAT, T, false>), dim3(flat), dim3(kBlock), 0, s, a);
         return;
     }
