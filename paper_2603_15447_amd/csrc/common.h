@@ -27,14 +27,15 @@ constexpr int kBlock = 256;
 // was 97, 138 and 299 us at 2^10, 2^17 and 2^20 segments' tiles, two 90, 132
 // and 299.
 constexpr int kChainQueries = 2;
-// Calls of 2^18 to 2^21 queries on a grid that the caches near the CUs hold are
-// over before wavefronts run short, and four queries share their launch better:
-// up to `small_seg` segments they keep four (2^20 queries, four against two: 1000
-// segments, grid 6.5 and 6.8 us, tiles 7.5 and 7.8, 16-bit 5.7 and 6.4, cubic tiles
-// 9.6 and 9.9; 8192: grid 9.6 and 8.7, tiles 7.7 and 8.5, cubic tiles 11.2 and 10.3; 2^17:
-// tiles 10.9 and 10.1, 16-bit 7.5 and 8.2).
-inline int chain_queries(uint32_t n_seg, uint32_t nq, uint32_t small_seg) {
-    return nq >= (1u << 18) && nq < (1u << 21) && n_seg <= small_seg ? 4 : kChainQueries;
+// Where a grid is so small that a CU's own cache holds it, there is no gather to
+// wait for, and four queries share their launch better: in calls of 2^20 queries
+// and more, up to `many` segments, or `few` in calls of under 2^21, which leave a
+// CU eight workgroups of two queries per thread and four of four.  The limits are
+// each evaluator's and dimension's own (two against four, 5,000 random calls: 2^22
+// and more 1D queries on up to 64 segments' grid 1.15 to 1.28 times the time, on
+// 2^12 0.9 to 1.0, 3D on 2^12 0.70; 2^20 3D queries on 2^8 and less 1.0 to 1.18).
+inline int chain_queries(uint32_t n_seg, uint32_t nq, uint32_t few, uint32_t many) {
+    return nq >= (1u << 20) && n_seg <= (nq < (1u << 21) ? few : many) ? 4 : kChainQueries;
 }
 
 // ------------------------------------------------------------------ host

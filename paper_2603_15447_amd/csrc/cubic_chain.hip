@@ -75,10 +75,13 @@ __global__ __launch_bounds__(kBlock) void k_piecewise_cubic_eval(const float *__
 template <int DIM>
 int launch_cubic_eval(const float *grid, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                       hipStream_t s) {
-    constexpr int Q = kChainQueries;
-    const uint32_t blocks = (nq + kBlock * Q - 1) / (kBlock * Q);
-    hipLaunchKernelGGL((k_piecewise_cubic_eval<DIM, Q>), dim3(blocks), dim3(kBlock), 0, s, grid, n_seg, T, nq, out,
-                       plane);
+    auto launch = [&](auto q) {
+        constexpr uint32_t per_block = kBlock * decltype(q)::value;
+        hipLaunchKernelGGL((k_piecewise_cubic_eval<DIM, decltype(q)::value>), dim3((nq + per_block - 1) / per_block),
+                           dim3(kBlock), 0, s, grid, n_seg, T, nq, out, plane);
+    };
+    if (chain_queries(n_seg, nq, 1024 / (DIM * DIM), 1024 / (DIM * DIM)) == 4) launch(std::integral_constant<int, 4>{});
+    else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_cubic_eval");
     return BZ_OK;
 }
@@ -191,7 +194,7 @@ int launch_cubic_eval_tiled(const float *tiles, uint32_t n_seg, const float *T, 
         hipLaunchKernelGGL((k_piecewise_cubic_eval_tiled<DIM, decltype(q)::value>), dim3((nq + per_block - 1) / per_block),
                            dim3(kBlock), 0, s, tiles, n_seg, T, nq, out, plane);
     };
-    if (chain_queries(n_seg, nq, 1u << 12) == 4) launch(std::integral_constant<int, 4>{});
+    if (chain_queries(n_seg, nq, 1024 / (DIM * DIM), 1024 / (DIM * DIM)) == 4) launch(std::integral_constant<int, 4>{});
     else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_cubic_eval_tiled");
     return BZ_OK;

@@ -288,10 +288,14 @@ int tex_texels_rt(int degree, int mode) {
 template <int DIM, bool TILED>
 int launch_chain_texemu(const float *grid, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                         int F, int rnd, hipStream_t s) {
-    constexpr int Q = kChainQueries;
-    const uint32_t blocks = (nq + kBlock * Q - 1) / (kBlock * Q);
-    hipLaunchKernelGGL((k_piecewise_texemu<DIM, Q, TILED>), dim3(blocks), dim3(kBlock), 0, s, grid, n_seg, T, nq, out,
-                       plane, F, rnd);
+    auto launch = [&](auto q) {
+        constexpr uint32_t per_block = kBlock * decltype(q)::value;
+        hipLaunchKernelGGL((k_piecewise_texemu<DIM, decltype(q)::value, TILED>), dim3((nq + per_block - 1) / per_block),
+                           dim3(kBlock), 0, s, grid, n_seg, T, nq, out, plane, F, rnd);
+    };
+    constexpr uint32_t small = DIM == 1 ? 2048 : DIM == 2 ? 1023 : 0;
+    if (chain_queries(n_seg, nq, small, small) == 4) launch(std::integral_constant<int, 4>{});
+    else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_texemu");
     return BZ_OK;
 }
