@@ -7,6 +7,8 @@
 //                  the v basis once per grid column (isoline coefficients
 //                  R_i(v_b), shared through LDS with the u basis of its rows),
 //                  then du+1 FMAs per coordinate and point.
+//  k_tensor_grid_patch  calls of few patches, rows or long columns: a patch per
+//                  workgroup.
 //  k_tensor_points_staged  surfaces at random (u,v) per query: a run of queries
 //                  per workgroup, their objects' nets in LDS, v -> u per lane.
 //  k_tensor_points one object per wavefront, random (u,v,w) per query, 4
@@ -314,6 +316,143 @@ GridArgs grid_args(int nu, int nv, int64_t n_obj, int64_t plane) {
     g.div_cb = make_fastdiv(g.cb);
     g.div_npts = make_fastdiv(g.npts);
     return g;
+}
+
+// One patch per workgroup, without tables of the columns (grid_by_patch says
+// where): where nv divides the block size every thread keeps one grid column b,
+// contracts the net with the v basis once (isoline coefficients R_i(v_b)) and
+// evaluates its points of that column with the u basis of their rows, from a
+// table in LDS when nu <= block size; else every point on its own.  NU, NV > 0 fix
+// the grid size at compile time: the row loop unrolls, with du = dv the column
+// basis is a row of the same table, and each column is contracted once, by one
+// thread, and shared with the other threads of that column through LDS; 0 takes
+// nu, nv at run time.  The same basis at the same parameters a/(nu-1), b/(nv-1) as
+// k_tensor_grid, in the same order: the same bits.
+template <int DU, int DV, int DIM, typename T, int BASIS, int NU, int NV>
+__device__ __forceinline__ void grid_columns(const T *__restrict__ P, int nu_rt, int nv_rt, float du_den, float dv_den,
+                                             float *__restrict__ ob, int64_t plane, float *tab_u) {
+    constexpr int NCP = (DU + 1) * (DV + 1);
+    const int nu = NU > 0 ? NU : nu_rt;
+    const int nv = NV > 0 ? NV : nv_rt;
+    const int b = threadIdx.x % nv;
+    const int a0 = threadIdx.x / nv;
+    const int astep = kBlock / nv;
+    const bool table = nu <= kBlock;
+    if (table) {
+        if (static_cast<int>(threadIdx.x) < nu) {
+            float Bu[DU + 1];
+            basis_at<DU, BASIS>(static_cast<float>(threadIdx.x) / du_den, Bu);
+#pragma unroll
+            for (int i = 0; i <= DU; ++i) tab_u[threadIdx.x * (DU + 1) + i] = Bu[i];
+        }
+        __syncthreads();
+    }
+    // isoline coefficients of column b: R[c][i] = sum_j Bv_j(b) P[c][i][j]
+    auto contract = [&](float (&R)[DIM][DU + 1]) {
+        float Bv[DV + 1];
+        if constexpr (NU > 0 && NU == NV && DU == DV) {
+#pragma unroll
+            for (int j = 0; j <= DV; ++j) Bv[j] = tab_u[b * (DU + 1) + j];
+        } else {
+            basis_at<DV, BASIS>(static_cast<float>(b) / dv_den, Bv);
+        }
+#pragma unroll
+        for (int c = 0; c < DIM; ++c)
+#pragma unroll
+            for (int i = 0; i <= DU; ++i) {
+                float acc = Bv[0] * to_f32<T>(P[c * NCP + i * (DV + 1)]);
+#pragma unroll
+                for (int j = 1; j <= DV; ++j)
+                    acc = __builtin_fmaf(Bv[j], to_f32<T>(P[c * NCP + i * (DV + 1) + j]), acc);
+                R[c][i] = acc;
+            }
+    };
+    float R[DIM][DU + 1];
+    if constexpr (NU > 0) {
+        static_assert(NU <= kBlock && NU % (kBlock / NV) == 0, "fixed grids fill whole row steps");
+        // the first NV threads contract one column each; the kBlock / NV
+        // threads of a column share it through LDS
+        __shared__ __align__(16) float tab_r[NV * DIM * (DU + 1)];
+        if (static_cast<int>(threadIdx.x) < NV) {
+            float Rc[DIM][DU + 1];
+            contract(Rc);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c)
+#pragma unroll
+                for (int i = 0; i <= DU; ++i) tab_r[(b * DIM + c) * (DU + 1) + i] = Rc[c][i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < DIM; ++c)
+#pragma unroll
+            for (int i = 0; i <= DU; ++i) R[c][i] = tab_r[(b * DIM + c) * (DU + 1) + i];
+        const uint32_t lo = static_cast<uint32_t>(a0 * NV + b);
+#pragma unroll
+        for (int k = 0; k < NU / (kBlock / NV); ++k) {
+            const int a = a0 + k * (kBlock / NV);
+            float Bu[DU + 1];
+#pragma unroll
+            for (int i = 0; i <= DU; ++i) Bu[i] = tab_u[a * (DU + 1) + i];
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) st_stream(ob + c * plane + (lo + k * kBlock), dot_basis<DU>(Bu, R[c]));
+        }
+        return;
+    }
+    contract(R);
+    float *__restrict__ oc = ob + a0 * nv + b;
+    if (table) {
+        for (int a = a0; a < nu; a += astep, oc += kBlock) {
+            float Bu[DU + 1];
+#pragma unroll
+            for (int i = 0; i <= DU; ++i) Bu[i] = tab_u[a * (DU + 1) + i];
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) st_stream(oc + c * plane, dot_basis<DU>(Bu, R[c]));
+        }
+    } else {
+        for (int a = a0; a < nu; a += astep, oc += kBlock) {
+            float Bu[DU + 1];
+            basis_at<DU, BASIS>(static_cast<float>(a) / du_den, Bu);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) st_stream(oc + c * plane, dot_basis<DU>(Bu, R[c]));
+        }
+    }
+}
+
+template <int DU, int DV, int DIM, typename T, int BASIS>
+__global__ __launch_bounds__(kBlock) void k_tensor_grid_patch(const T *__restrict__ ctrl, int nu, int nv,
+                                                        float *__restrict__ out, int64_t plane, int64_t o0) {
+    constexpr int NCP = (DU + 1) * (DV + 1);
+    const uint32_t o = blockIdx.x;
+    const T *__restrict__ P = ctrl + static_cast<size_t>(o) * DIM * NCP;
+    const int npts = nu * nv;
+    float *__restrict__ ob = out + (o0 + o) * static_cast<int64_t>(npts);
+    const float du_den = nu > 1 ? static_cast<float>(nu - 1) : 1.0f;
+    const float dv_den = nv > 1 ? static_cast<float>(nv - 1) : 1.0f;
+    __shared__ __align__(16) float tab_u[kBlock * (DU + 1)];
+    if (kBlock % nv == 0) {
+        if (nu == 32 && nv == 32) grid_columns<DU, DV, DIM, T, BASIS, 32, 32>(P, nu, nv, du_den, dv_den, ob, plane, tab_u);
+        else grid_columns<DU, DV, DIM, T, BASIS, 0, 0>(P, nu, nv, du_den, dv_den, ob, plane, tab_u);
+    } else {
+        for (int p = threadIdx.x; p < npts; p += kBlock) {
+            const int a = p / nv, b = p - (p / nv) * nv;
+            float Bu[DU + 1], Bv[DV + 1];
+            basis_at<DU, BASIS>(static_cast<float>(a) / du_den, Bu);
+            basis_at<DV, BASIS>(static_cast<float>(b) / dv_den, Bv);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                float Ri[DU + 1];
+#pragma unroll
+                for (int i = 0; i <= DU; ++i) {
+                    float acc = Bv[0] * to_f32<T>(P[c * NCP + i * (DV + 1)]);
+#pragma unroll
+                    for (int j = 1; j <= DV; ++j)
+                        acc = __builtin_fmaf(Bv[j], to_f32<T>(P[c * NCP + i * (DV + 1) + j]), acc);
+                    Ri[i] = acc;
+                }
+                st_stream(ob + c * plane + p, dot_basis<DU>(Bu, Ri));
+            }
+        }
+    }
 }
 
 // ------------------------------------------------------------------ VALU points
@@ -636,9 +775,34 @@ __global__ __launch_bounds__(kBlock, 4) void k_tensor_points_mfma(const T *__res
 }
 
 // ------------------------------------------------------------------ dispatch (over degrees and dim)
+// Whether a grid call takes a workgroup per patch (k_tensor_grid_patch) rather
+// than chunks of the output with tables (k_tensor_grid).  A patch per workgroup
+// has no tables to fill before its first point, which calls of few patches and
+// grids of one to three rows (a column's contraction serves no others) show; its
+// stores begin where a patch begins, and small patches leave its threads idle, so
+// large calls go in chunks, but for grids whose nv divides the block size and whose
+// columns are long enough.  By patches, points and control points of a patch, from
+// 5,000 random calls on rotating buffers: so chosen they take 1.1 % more time than
+// with the better kernel each, all in chunks 6 % more (7805 patches x 32 x 32 in
+// 1D: 6.5 us by patch, 10.7 in chunks; 5 patches x 8 x 31 in 4D: 2.1 and 3.0; 8417
+// x 1 x 191 in 3D: 8.1 and 21.7; 33 x 33 points of 16384 patches: 75 and 35).
+inline bool grid_by_patch(int nu, int nv, int64_t n, int ncp, int dim, bool f32) {
+    const int64_t pts = static_cast<int64_t>(nu) * nv, work = n * pts * ncp;
+    if (nu == 32 && nv == 32) return true;
+    if (nu <= (f32 ? 3 : 2) && dim > 1 && pts < 2048 && pts >= (nu == 1 ? 64 : 256)) return true;
+    if (kBlock % nv == 0) return pts >= 2048 ? n >= 256 : pts >= 1024 ? n >= 128 : n < (pts >= 256 ? 1024 : 256);
+    if (pts >= 2048) return false;
+    return pts >= 1024 ? n == 1 || (n >= 64 && work < 1 << 22) : n < 2048 && work < (f32 ? 1 << 22 : 1 << 21);
+}
+
 template <typename T, int BASIS, int DU, int DV, int DIM>
 void launch_grid3(const void *ctrl, int nu, int nv, float *out, int64_t plane, int64_t o0, uint32_t n_obj,
                   hipStream_t s) {
+    if (grid_by_patch(nu, nv, n_obj, (DU + 1) * (DV + 1), DIM, std::is_same<T, float>::value)) {
+        hipLaunchKernelGGL((k_tensor_grid_patch<DU, DV, DIM, T, BASIS>), dim3(n_obj), dim3(kBlock), 0, s,
+                           static_cast<const T *>(ctrl), nu, nv, out, plane, o0);
+        return;
+    }
     GridArgs g = grid_args<DU, DIM>(nu, nv, n_obj, plane);
     const size_t lds = sizeof(float) * grid_floats<DU, DIM>(g);
     const int64_t npts = static_cast<int64_t>(nu) * nv;
