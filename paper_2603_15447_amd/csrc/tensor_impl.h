@@ -469,11 +469,15 @@ __global__ __launch_bounds__(kBlock) void k_tensor_points(const T *__restrict__ 
                                                           int64_t o0) {
     constexpr int NCP = (DU + 1) * (DV + 1) * (DW + 1);
     const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
-    const uint32_t o = w / waves_per_obj;
+    uint32_t o = w, part = 0;
+    if (waves_per_obj > 1) {  // (the division is a good part of what a small object takes)
+        o = w / waves_per_obj;
+        part = w - o * waves_per_obj;
+    }
     if (o >= n_obj) return;
     const int lane = threadIdx.x & 63;
     const T *__restrict__ P = ctrl + static_cast<size_t>(o) * DIM * NCP;
-    const int64_t j_begin = static_cast<int64_t>(w - o * waves_per_obj) * per_wave * (64 * kPtsQ);
+    const int64_t j_begin = static_cast<int64_t>(part) * per_wave * (64 * kPtsQ);
     const int64_t j_end = min(n_per, j_begin + static_cast<int64_t>(per_wave) * (64 * kPtsQ));
     for (int64_t j0 = j_begin; j0 < j_end; j0 += 64 * kPtsQ) {
         float Bu[kPtsQ][DU + 1], Bv[kPtsQ][DV + 1], Bw[kPtsQ][DW + 1];
