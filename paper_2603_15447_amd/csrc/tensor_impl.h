@@ -658,16 +658,19 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // for tricubic points contracted either way.
 template <int D>
 __device__ __forceinline__ void bernstein_basis_comp(float t, float (&B)[D + 1]) {
-    const float s = 1.0f - t, d = (1.0f - s) - t, ds = d == d ? d : 0.0f;  // (t infinite: nothing lost)
+    const float s = 1.0f - t, ds = (1.0f - s) - t;
     if constexpr (D == 1) {
         B[0] = s;
         B[1] = t;
     } else {
-        const float s2 = __builtin_fmaf(s, s, (s + s) * ds), t2 = t * t;
+        // what a loss adds; not a number where t is infinite or next to it: nothing
+        // is lost there, and the basis has its infinite values
+        auto add = [](float x) { return x == x ? x : 0.0f; };
+        const float s2 = __builtin_fmaf(s, s, add((s + s) * ds)), t2 = t * t;
         if constexpr (D == 2) {
             const float a = 2.0f * t;
             B[0] = s2;
-            B[1] = __builtin_fmaf(a, ds, a * s);
+            B[1] = __builtin_fmaf(a, s, add(a * ds));
             B[2] = t2;
         } else {
             B[0] = s2 * s;
