@@ -199,6 +199,7 @@ struct bz_plan_s {
     uint16_t *ntab = nullptr;
     float *nknots = nullptr;
     void *npts = nullptr;
+    bool wide_knots = false;
     unsigned int *counters = nullptr;
     std::vector<ClassInfo> classes;
     std::vector<int32_t> perm_h;  // host copy of perm (window boundaries of the tile order)
@@ -249,6 +250,7 @@ int launch_batch(const bz_plan_s *p, const float *t, const float *v, float *out,
     a.ntab = p->ntab;
     a.nknots = p->nknots;
     a.npts = p->npts;
+    a.wide_knots = p->wide_knots;
     a.t = t;
     a.v = v;
     a.out = out;
@@ -472,6 +474,7 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
         std::vector<uint16_t> ntab;
         std::vector<float> nknots;
         int64_t n_segs = 0, n_pts = 0;
+        bool wide_knots = false;
         if (any_nurbs) {
             if (!knot_offset || !knots) return fail(BZ_ERR_NULL, "%s: knot_offset and knots are required for NURBS", fn);
             ko.resize(n_obj + 1);
@@ -501,6 +504,7 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
                 spans.clear();
                 for (int64_t i = kNurbsP; i < ncp; ++i)
                     if (u[i] < u[i + 1]) spans.push_back(static_cast<int32_t>(i));
+                for (int32_t i : spans) wide_knots = wide_knots || knots_wide(u + i - 2);
                 if (!add_nurbs(u, ncp, spans, n_pts, nhead, ntab, buckets)) return fail(BZ_ERR_INTERNAL, "%s: NURBS span table", fn);
                 nknots.insert(nknots.end(), u, u + nk);
                 n_segs += static_cast<int64_t>(spans.size());
@@ -520,6 +524,7 @@ int bz_batch_plan_create(int64_t n_obj, const uint16_t *kind_degree, const int64
         p->classes = cls;
         for (const ClassInfo &ci : cls) p->has_patches = p->has_patches || ci.kind == 4;
         p->n_segs = n_segs;
+        p->wide_knots = wide_knots;
         const int es = dtype_size(dtype);
         auto dmalloc = [&](void **ptr, size_t bytes) -> int {
             hipError_t e = hipMalloc(ptr, std::max<size_t>(bytes, 16));
