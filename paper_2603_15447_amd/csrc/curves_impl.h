@@ -505,7 +505,7 @@ __global__ __launch_bounds__(kBlock) void k_to_seiler(const T *__restrict__ ctrl
 // than with the better kernel each, all staged 16 % more, all with one thread per
 // query 7 % (118 rational curves of degree 5 in 3D, BF16, x 45: 2.3 us with a
 // thread per query, 3.3 staged; 9754 of degree 15 in 4D, FP16, Seiler form x 36:
-// 10.7 and 5.6; 100,003 rational quintics x 50: 22.0 either way).
+// 10.7 and 5.6; 100,003 rational quintics x 50: 21.9 and 21.5).
 // Curves of fewer than kMixedMinT queries are never staged (3,000,000 cubics x 1:
 // 30 us with a thread per query, 36 staged).
 constexpr uint32_t kMixedMinT = 8;
@@ -527,7 +527,8 @@ void launch_curves_dd(CurveArgs a, hipStream_t s) {
             return;
         }
     }
-    const int from = staged_log2<F, RAT, D>() - (n_t % 64 == 0 ? (F == FORM_SEILER ? 1 : 2) : 0) + (n_t < 12 ? 2 : 0);
+    const int from = staged_log2<F, RAT, D>() + (n_t < 12 ? 2 : 0) -
+                     (n_t % 64 == 0 ? (F == FORM_SEILER ? 1 : 2) : RAT && F == FORM_BERN && n_t >= 40 ? 1 : 0);
     if (n_t < kMixedMinT || a.t_in_out || a.nq < 1u << from) {
         hipLaunchKernelGGL((k_curves<D, DIM, F, RAT, T, false>), dim3(flat), dim3(kBlock), 0, s, a);
         return;
