@@ -405,8 +405,8 @@ int bz_batch_eval_uv(bz_plan plan, const float *t, const float *v, float *out, b
  * autotuning a plan launches 64 workgroups per CU with the static schedule and
  * tiles chosen by n_t and the batch's size: 4 sub-tiles, four parameters per
  * lane and windows of 2^17 objects when n_t is a multiple of 16 (de Casteljau: 2
- * sub-tiles, and one parameter per lane in batches of fewer than 16 tiles of 2048
- * queries per CU), smaller windows and one parameter per lane for short or odd
+ * sub-tiles, or one parameter per lane, where the highest degree's tiles would
+ * outlast the batch), smaller windows and one parameter per lane for short or odd
  * rows, smaller tiles where a batch is too small to give every CU one.  No launch
  * has more workgroups than tiles.
  * Synchronises the stream.  best6 (nullable, host, 6 values): workgroups,

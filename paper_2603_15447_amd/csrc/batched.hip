@@ -143,17 +143,32 @@ struct Layout {
 // with 4 x 4, 138 with 4 x 1; 400,000 x 12: 82 and 68), and of longer ones two
 // sub-tiles do better than four (300,000 x 24: 64 us, 72 with four or with one
 // query per lane).
-// De Casteljau is quadratic in the degree: 4 x 4 queries of degree 15 in turn are a
-// long tail until every CU has 16 tiles of 2048 queries, and 2 x 4 suffice from
-// there on (34,800 curves and NURBS x 16, FP32: 34 us with 4 x 4, 14 with 4 x 1;
-// 278,500: 68 and 60; 1.1 million: 221 with 4 x 4, 213 with 4 x 1, 201 with 2 x 4).
+// De Casteljau is quadratic in the degree, and rows of n_t % 16 == 0 take four
+// queries per lane once the launch is long beside its heaviest tile: batches of up
+// to degree 7 from two tiles of 4096 queries per CU on, 4 x 4; of up to 12 from
+// four of 2048 on, 2 x 4, and 4 x 4 again from 16 of 4096; of up to 15 from twelve
+// of 2048, 2 x 4 (FP32, curves and NURBS x 16 on rotating inputs: 262,144 of up to
+// degree 5, 4 x 4 23.0 us, 2 x 4 25.9, 4 x 1 30.4; 262,144 of up to 12, 43, 42 and
+// 42; 393,216 73, 65 and 77; 393,216 of up to 15, 90, 79 and 87; 16,384 of up to
+// 15, 33, 19 and 13).  Other rows: 4 x 4 queries of degree 15 in turn are a long
+// tail until every CU has 16 tiles of 2048 queries, and 2 x 4 suffice from there on.
 Layout default_layout(const std::vector<ClassInfo> &cls, int method, int64_t n_t, uint32_t cus) {
     std::vector<Layout> choices;
     if (method == BZ_DECASTELJAU && n_t % 4 == 0 && n_t >= 16) {
         const uint32_t win = n_t % 16 == 0 ? 1u << 17 : 1u << 15;
         int64_t queries = 0;
-        for (const ClassInfo &ci : cls) queries += ci.count * n_t;
-        if (queries >= static_cast<int64_t>(cus) * 16 * 2048) return {2, 4, win};
+        int degree = 1;
+        for (const ClassInfo &ci : cls) {
+            queries += ci.count * n_t;
+            degree = std::max(degree, ci.kind == 4 ? 6 : ci.degree);  // (a bicubic patch: 3 + 3)
+        }
+        const int64_t per_cu = queries / cus;
+        if (n_t % 16 == 0) {
+            if (per_cu >= 4096 * (degree <= 7 ? 2 : 16) && degree <= 12) return {4, 4, win};
+            if (per_cu >= 2048 * (degree <= 12 ? 4 : 12) && degree > 7) return {2, 4, win};
+        } else if (per_cu >= 2048 * 16) {
+            return {2, 4, win};
+        }
         choices = {{4, 1, win}, {2, 1, win}, {1, 1, win}};
     } else if (n_t % 16 == 0) choices = {{4, 4, 1u << 17}, {4, 1, 1u << 17}, {2, 1, 1u << 17}, {1, 1, 1u << 17}};
     else if (n_t > 16 && n_t % 4 == 0) choices = {{2, 4, 1u << 15}, {4, 1, 1u << 15}, {2, 1, 1u << 15}, {1, 1, 1u << 15}};
