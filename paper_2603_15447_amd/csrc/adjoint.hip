@@ -133,38 +133,38 @@ __global__ __launch_bounds__(kBlock) void k_fit_step(FitArgs a) {
     float mine = 0.0f, loss_sum = 0.0f;
     // blocks of kFitSpl samples per lane (see there)
     for (int64_t j0 = 0; j0 == 0 || j0 < a.n_t; j0 += kFitSpl * L) {
-    const int64_t j1 = min(a.n_t, j0 + kFitSpl * L);
-    float gb[DIM][D + 1] = {};
-    float loss = 0.0f;
-    for (int64_t j = j0 + sub; live && j < j1; j += L) {
-        const int64_t q = c * a.n_t + j;
-        const float t = a.t[q];
-        float mt = a.m_t[q], vt = a.v_t[q];
-        float yv[DIM];
+        const int64_t j1 = min(a.n_t, j0 + kFitSpl * L);
+        float gb[DIM][D + 1] = {};
+        float loss = 0.0f;
+        for (int64_t j = j0 + sub; live && j < j1; j += L) {
+            const int64_t q = c * a.n_t + j;
+            const float t = a.t[q];
+            float mt = a.m_t[q], vt = a.v_t[q];
+            float yv[DIM];
 #pragma unroll
-        for (int k = 0; k < DIM; ++k) yv[k] = a.y[k * a.plane + q];
-        float B[D + 1], W, C[DIM], dC[DIM];
-        curve_and_derivative<D, DIM, false>(b, wv, t, B, W, C, dC);
-        float dt = 0.0f;
+            for (int k = 0; k < DIM; ++k) yv[k] = a.y[k * a.plane + q];
+            float B[D + 1], W, C[DIM], dC[DIM];
+            curve_and_derivative<D, DIM, false>(b, wv, t, B, W, C, dC);
+            float dt = 0.0f;
 #pragma unroll
-        for (int k = 0; k < DIM; ++k) {
-            const float r = C[k] - yv[k];
-            loss = __builtin_fmaf(r, r, loss);
-            const float g = 2.0f * r * a.inv_m;
-            dt = __builtin_fmaf(g, dC[k], dt);
+            for (int k = 0; k < DIM; ++k) {
+                const float r = C[k] - yv[k];
+                loss = __builtin_fmaf(r, r, loss);
+                const float g = 2.0f * r * a.inv_m;
+                dt = __builtin_fmaf(g, dC[k], dt);
 #pragma unroll
-            for (int i = 0; i <= D; ++i) gb[k][i] = __builtin_fmaf(g, B[i], gb[k][i]);
+                for (int i = 0; i <= D; ++i) gb[k][i] = __builtin_fmaf(g, B[i], gb[k][i]);
+            }
+            float tn = adam(t, dt, &mt, &vt, a);
+            tn = tn < 0.0f ? 0.0f : (tn > 1.0f ? 1.0f : tn);
+            a.t[q] = tn;
+            a.m_t[q] = mt;
+            a.v_t[q] = vt;
         }
-        float tn = adam(t, dt, &mt, &vt, a);
-        tn = tn < 0.0f ? 0.0f : (tn > 1.0f ? 1.0f : tn);
-        a.t[q] = tn;
-        a.m_t[q] = mt;
-        a.v_t[q] = vt;
-    }
-    loss = CPW == 2 ? half_sum(loss) : wave_sum(loss);
-    const float blk = reduce_grads<D, DIM, CPW>(gb, sub);
-    loss_sum = j0 == 0 ? loss : loss_sum + loss;
-    mine = j0 == 0 ? blk : mine + blk;
+        loss = CPW == 2 ? half_sum(loss) : wave_sum(loss);
+        const float blk = reduce_grads<D, DIM, CPW>(gb, sub);
+        loss_sum = j0 == 0 ? loss : loss_sum + loss;
+        mine = j0 == 0 ? blk : mine + blk;
     }
     if (a.loss_part && sub == 0 && live) a.loss_part[c] = loss_sum * a.inv_m;
     if (sub < NP && live) {

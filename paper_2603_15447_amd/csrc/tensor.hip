@@ -5,8 +5,14 @@
 //                  with the v basis once per grid column (isoline control
 //                  points R_i(v_b), in LDS beside the u basis of its rows), then
 //                  du+1 FMAs per coordinate and point.
-//  k_tensor_points one object per wavefront, random (u,v[,w]) per query,
-//                  4 queries per lane, separable contraction w -> v -> u.
+//  k_tensor_grid_patch  a patch per workgroup, for calls of few patches, few rows
+//                  or long columns.
+//  k_tensor_points_staged  surfaces at random (u,v) per query: runs of queries,
+//                  their objects' nets in LDS.
+//  k_tensor_points volumes at random (u,v,w) per query, one object per wavefront
+//                  (or a part of one), 4 queries per lane, separable contraction
+//                  w -> v -> u.
+//  k_tensor_points_mfma  volumes of degrees 2 and 3, w on the FP32 matrix cores.
 //  k_tensor_mfma   bicubic 32x32 grids as a dense contraction on the matrix
 //                  cores: D[(patch,coord)][grid pt] = P[(patch,coord)][16] x
 //                  K[16][grid pt] with K the Kronecker product of the u and v

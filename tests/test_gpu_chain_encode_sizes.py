@@ -1,8 +1,8 @@
-"""GPU: the chain encoder at the edges of its launch rules -- the columns of a
-thread (4) and of a block (512 or 2048), the longest chain that goes in one
-launch (8192 columns), the change of block size (2^18 columns) and the longest
-chain whose blocks add up their predecessors' partials (4096 blocks) --
-against the FP64 oracle's encoding."""
+"""GPU: the chain encoder at sizes on both sides of its blocks and launches -- the
+columns of a thread (4) and of a block (512 or 2048), chains of one block and of
+several in one launch (up to 2^15 columns), the change of block size (2^18
+columns), and more blocks than the scan takes at once -- against the FP64
+oracle's encoding."""
 import numpy as np
 import pytest
 

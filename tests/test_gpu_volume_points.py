@@ -1,6 +1,5 @@
-"""GPU: scattered points of volumes on the matrix cores -- every pair of
-degrees it takes, objects of fewer than, exactly and just over 64 points,
-several wavefronts per object and several steps per wavefront, 16-bit storage,
+"""GPU: scattered points of volumes on the matrix cores -- degrees 2 and 3,
+objects of fewer than, exactly and just over 64 points, several wavefronts per object and several steps per wavefront, 16-bit storage,
 parameters outside [0, 1] and not finite -- against the FP64 oracle; and
 surfaces' points over several wavefronts per object."""
 import numpy as np
@@ -38,7 +37,7 @@ def test_storage_widens_exactly(dtype):
 def test_outside_and_not_finite(orc):
     P, uvw = _problem(9, 100, 2, 3, 3, 3, seed=9, lo=-1.0, hi=2.0)
     ref = orc.tensor_points(P, 2, 3, 3, uvw)
-    # outside [0, 1] the basis grows: sum |B| is at most 5^2 * 5^3 * 5^3 there (|1-t| + |t| <= 3 per factor: 3^8)
+    # outside [0, 1] the basis grows: sum |B| is at most 3^8 there (|1-t| + |t| <= 3 per factor)
     got = host(bz.eval_tensor_patch(to_dev(P), 2, 3, 3, uvw=to_dev(uvw)))
     assert np.abs(got - ref).max() <= 40 * 2.0 ** -24 * 3 ** 8
     bad = uvw.copy()
