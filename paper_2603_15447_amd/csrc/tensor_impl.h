@@ -787,19 +787,30 @@ __global__ __launch_bounds__(kBlock, 4) void k_tensor_points_mfma(const T *__res
 // has no tables to fill before its first point, which calls of few patches and
 // grids of one to three rows (a column's contraction serves no others) show; its
 // stores begin where a patch begins, and small patches leave its threads idle, so
-// large calls go in chunks, but for grids whose nv divides the block size and whose
-// columns are long enough.  By patches, points and control points of a patch, from
-// 5,000 random calls on rotating buffers: so chosen they take 1.1 % more time than
-// with the better kernel each, all in chunks 6 % more (7805 patches x 32 x 32 in
-// 1D: 6.5 us by patch, 10.7 in chunks; 5 patches x 8 x 31 in 4D: 2.1 and 3.0; 8417
-// x 1 x 191 in 3D: 8.1 and 21.7; 33 x 33 points of 16384 patches: 75 and 35).
+// large calls go in chunks, but for 1D points and for few rows of a nv that divides
+// the block size, where a thread has one column and few points of it.  By patches,
+// points, control points of a patch and floats of output, from 5,000 random calls
+// of up to 2^24 points, 2,500 more of up to 2^26 with such nv and 2,500 of 1024 points
+// a patch about, on rotating buffers: so chosen they take 1 % more time than with the better kernel each, all
+// in chunks 6 to 8 % more (7805 patches x 32 x 32 in 1D: 6.5 us by patch, 10.7 in
+// chunks; 5 patches x 8 x 31 in 4D: 2.1 and 3.0; 8417 x 1 x 191 in 3D: 8.1 and
+// 21.7; 4096 x 32 x 32 in 2D 6.9 and 8.7, 65536 of them 88 and 80; 8000 x 64 x 64
+// in 2D 114 and 94; 33 x 33 points of 16384 patches 75 and 35).  16-bit nets of 25
+// control points are the slow ones of run-time rows by patch (2276 x 128 x 8 in 3D:
+// 13.7 and 6.1).
 inline bool grid_by_patch(int nu, int nv, int64_t n, int ncp, int dim, bool f32) {
-    const int64_t pts = static_cast<int64_t>(nu) * nv, work = n * pts * ncp;
-    if (nu == 32 && nv == 32) return true;
+    const int64_t pts = static_cast<int64_t>(nu) * nv, work = n * pts * ncp, floats = n * pts * dim;
+    if (nu == 32 && nv == 32) return dim == 1 || floats < 1 << 24;
     if (nu <= (f32 ? 3 : 2) && dim > 1 && pts < 2048 && pts >= (nu == 1 ? 64 : 256)) return true;
-    if (kBlock % nv == 0) return pts >= 2048 ? n >= 256 : pts >= 1024 ? n >= 128 : n < (pts >= 256 ? 1024 : 256);
+    if (kBlock % nv == 0) {
+        if (!f32 && ncp >= 25 && nv <= 64) return false;
+        if (pts >= 1024)
+            return n >= (pts >= 2048 ? 256 : 128) && (dim == 1 || nu < 16 || floats < 1 << (pts >= 2048 ? 23 : 24));
+        return n < (pts >= 256 ? 1024 : 256) || (nu >= 4 && nv >= 128);
+    }
     if (pts >= 2048) return false;
-    return pts >= 1024 ? n == 1 || (n >= 64 && work < 1 << 22) : n < 2048 && work < (f32 ? 1 << 22 : 1 << 21);
+    if (pts >= 1024) return dim > 1 && ncp < (f32 ? 20 : 15) && (n == 1 || (n >= 96 && work < 1 << 22));
+    return n < 2048 && work < (f32 ? 1 << 22 : 1 << 21);
 }
 
 template <typename T, int BASIS, int DU, int DV, int DIM>

@@ -34,3 +34,16 @@ def test_many_and_few(orc, nu, nv, du, dv, dim, dtype):
     ref = orc.tensor_points(few, du, dv, 0, np.repeat(uv, 2, axis=0).astype(np.float32))
     # (the parameters a / (nu - 1) are rounded once on either side)
     assert bbox_err(got, ref, extents(few), nu * nv) <= TOL_F32
+
+
+# calls on either side of the output sizes up to which a workgroup takes a patch
+@pytest.mark.parametrize("nu,nv,dim,n", [(32, 32, 3, 5461), (32, 32, 3, 5462), (32, 32, 1, 20000), (64, 64, 2, 1023), (64, 64, 2, 1024),
+                                         (40, 32, 2, 6553), (40, 32, 2, 6554), (12, 256, 2, 1500), (16, 256, 2, 1500),
+                                         (4, 128, 3, 1500), (3, 128, 1, 1500), (33, 33, 3, 95), (33, 33, 3, 96)])
+@pytest.mark.parametrize("du,dv,dtype", [(3, 3, torch.float32), (4, 4, torch.float16), (2, 1, torch.bfloat16)])
+def test_large_and_few(nu, nv, dim, n, du, dv, dtype):
+    g = torch.Generator(device="cuda").manual_seed(n + du)
+    P = (torch.rand((n, dim, (du + 1) * (dv + 1)), generator=g, device="cuda") * 2 - 1).to(dtype)
+    whole = bz.eval_tensor_patch(P, du, dv, nu=nu, nv=nv).view(dim, n, nu * nv)
+    for a in [*range(0, n, max(1, n // 7)), n - 3]:
+        assert torch.equal(whole[:, a:a + 3], bz.eval_tensor_patch(P[a:a + 3], du, dv, nu=nu, nv=nv).view(dim, -1, nu * nv))
