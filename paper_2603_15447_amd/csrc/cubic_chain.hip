@@ -80,7 +80,8 @@ int launch_cubic_eval(const float *grid, uint32_t n_seg, const float *T, uint32_
         hipLaunchKernelGGL((k_piecewise_cubic_eval<DIM, decltype(q)::value>), dim3((nq + per_block - 1) / per_block),
                            dim3(kBlock), 0, s, grid, n_seg, T, nq, out, plane);
     };
-    if (chain_queries(n_seg, nq, 1024 / (DIM * DIM), 1024 / (DIM * DIM)) == 4) launch(std::integral_constant<int, 4>{});
+    constexpr uint32_t small = DIM == 1 ? 1024 : 0;
+    if (chain_queries(n_seg, nq, small, small) == 4) launch(std::integral_constant<int, 4>{});
     else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_cubic_eval");
     return BZ_OK;

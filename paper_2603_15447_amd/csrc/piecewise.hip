@@ -195,7 +195,7 @@ int launch_eval_tiled(const float *tiles, uint32_t n_seg, const float *T, uint32
         hipLaunchKernelGGL((k_piecewise_eval_tiled<DIM, decltype(q)::value>), dim3((nq + per_block - 1) / per_block),
                            dim3(kBlock), 0, s, tiles, n_seg, T, nq, out, plane);
     };
-    if (chain_queries(n_seg, nq, 8192 / (DIM * DIM), 4096 / (DIM * DIM * DIM)) == 4) launch(std::integral_constant<int, 4>{});
+    if (chain_queries(n_seg, nq, 8192 / (DIM * DIM), DIM < 4 ? 4096 / (DIM * DIM * DIM) : 0) == 4) launch(std::integral_constant<int, 4>{});
     else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_eval_tiled");
     return BZ_OK;
@@ -327,7 +327,7 @@ int launch_eval_tiled16(const uint16_t *tiles, uint32_t n_seg, const float *Tp, 
         hipLaunchKernelGGL((k_piecewise_eval_tiled16<DIM, H, decltype(q)::value>),
                            dim3((nq + per_block - 1) / per_block), dim3(kBlock), 0, s, tiles, n_seg, Tp, nq, out, plane);
     };
-    if (chain_queries(n_seg, nq, 8192, 8192 / (DIM * DIM * DIM)) == 4) launch(std::integral_constant<int, 4>{});
+    if (chain_queries(n_seg, nq, 8192, DIM < 3 ? 8192 / (DIM * DIM * DIM) : 0) == 4) launch(std::integral_constant<int, 4>{});
     else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_eval_tiled16");
     return BZ_OK;
@@ -368,7 +368,7 @@ template <int DIM>
 int launch_eval(const float *grid, uint32_t n_seg, const float *T, uint32_t nq, float *out, int64_t plane,
                 hipStream_t s) {
     const int qpt = piecewise_qpt();
-    switch (qpt ? qpt : chain_queries(n_seg, nq, 8192 / (DIM * DIM), 4096 / (DIM * DIM * DIM))) {
+    switch (qpt ? qpt : chain_queries(n_seg, nq, 8192 / (DIM * DIM), DIM < 4 ? 4096 / (DIM * DIM * DIM) : 0)) {
         case 1: return launch_eval_q<DIM, 1>(grid, n_seg, T, nq, out, plane, s);
         case 2: return launch_eval_q<DIM, 2>(grid, n_seg, T, nq, out, plane, s);
         case 8: return launch_eval_q<DIM, 8>(grid, n_seg, T, nq, out, plane, s);

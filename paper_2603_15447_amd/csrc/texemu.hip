@@ -293,8 +293,10 @@ int launch_chain_texemu(const float *grid, uint32_t n_seg, const float *T, uint3
         hipLaunchKernelGGL((k_piecewise_texemu<DIM, decltype(q)::value, TILED>), dim3((nq + per_block - 1) / per_block),
                            dim3(kBlock), 0, s, grid, n_seg, T, nq, out, plane, F, rnd);
     };
+    // (the filter's arithmetic wants more wavefronts in calls of under 6M queries: 161
+    // segments, 1.3M 1D queries 4.6 us with two, 5.4 with four; 436, 27M 71.3 and 65.0)
     constexpr uint32_t small = DIM == 1 ? 2048 : DIM == 2 ? 1023 : 0;
-    if (chain_queries(n_seg, nq, small, small) == 4) launch(std::integral_constant<int, 4>{});
+    if (nq >= (6u << 20) && chain_queries(n_seg, nq, 0, small) == 4) launch(std::integral_constant<int, 4>{});
     else launch(std::integral_constant<int, kChainQueries>{});
     BZ_CHECK_LAUNCH("k_piecewise_texemu");
     return BZ_OK;

@@ -28,3 +28,14 @@ def test_queries_per_thread(n_q, n_seg, dim):
               lambda x: bz.eval_piecewise_texemu_tiled(tiles, n_seg, dim, x)):
         once = f(short)
         assert torch.equal(f(t), once.repeat(1, n_q // short.numel() + 1)[:, :n_q])
+
+
+@pytest.mark.parametrize("n_q", [(6 << 20) - 1, 6 << 20])
+@pytest.mark.parametrize("n_seg,dim", [(2048, 1), (2049, 1), (1023, 2), (1024, 2), (1, 3)])
+def test_filter_queries_per_thread(n_q, n_seg, dim):
+    chain, T = bz_synth.chain_walk(n_seg=n_seg, dim=dim, n_q=1 << 16, seed=n_seg)
+    grid = bz.encode_piecewise(to_dev(chain))
+    tiles, short = bz.tile_piecewise(grid), to_dev(T)
+    t = short.repeat(n_q // short.numel() + 1)[:n_q].contiguous()
+    for f in (lambda x: bz.eval_piecewise_texemu(grid, x), lambda x: bz.eval_piecewise_texemu_tiled(tiles, n_seg, dim, x)):
+        assert torch.equal(f(t), f(short).repeat(1, n_q // short.numel() + 1)[:, :n_q])
