@@ -666,6 +666,8 @@ def suite_fit(torch, bz, bz_synth, cpu):
     loss = torch.zeros(n, device="cuda")
     bz.fit_adam_step(ctrl, t, y, mc, vc, mt, vt, 1, loss_part=loss)
     loss0 = float(loss.sum())
+    # a process's first launch also loads the kernel's code (about 2.5 ms)
+    bz.fit_adam_run(ctrl.clone(), t.clone(), y, mc.clone(), vc.clone(), mt.clone(), vt.clone(), 2, 1)
     s = torch.cuda.current_stream()
     a, bb = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     a.record(s)
@@ -697,7 +699,7 @@ def suite_fit(torch, bz, bz_synth, cpu):
                                                            "extrapolates to 200 times its time",
                                "run_200_steps_s": 200 * sec}
     return {"workload": "fit 65536 cubic 3D curves to 128 noisy samples each: fused L2 loss + adjoint + Adam, "
-                        "200 steps in one register-resident launch", "unit": "G sample-steps/s", **res}
+                        "200 steps in register-resident launches", "unit": "G sample-steps/s", **res}
 
 
 FORMS = ("decasteljau", "bernstein", "seiler")
